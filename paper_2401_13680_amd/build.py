@@ -12,9 +12,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpst.so")
 PROBE_LIB = os.path.join(HERE, "libpst_probe.so")
-# sha256 of the profile kernel's gfx950 instructions in the last build
+# sha256 of the profile kernels' gfx950 instructions in the last build
 KERNEL_HASH = os.path.join(HERE, "libpst.k_profile.sha256")
-SOURCES = ["pst_stats.hip", "pst_profile.hip", "pst_greedy.hip", "pst_label.hip", "pst_noalloc.hip", "pst_api.cpp",
+SOURCES = ["pst_stats.hip", "pst_profile.hip", "pst_stream.hip", "pst_greedy.hip", "pst_label.hip", "pst_noalloc.hip", "pst_api.cpp",
            "pst_sched.cpp"]
 
 HIPCC_FLAGS = [
@@ -56,26 +56,26 @@ def build_library(verbose: bool = False, probe: bool = False) -> str:
 
 
 def kernel_code_hash(hipcc: str) -> str:
-    """sha256 over the gfx950 instructions of every k_profile instantiation
-    (the device assembly between each kernel's label and its end, comments
-    dropped): it changes when the kernel's machine code does, not when a
-    comment or another kernel does."""
+    """sha256 over the gfx950 instructions of every instantiation of the profile
+    kernels k_stream and k_profile (the device assembly between each kernel's
+    label and its end, comments dropped): it changes when their machine code
+    does, not when a comment or another kernel does."""
     import hashlib
     import re
-    asm = subprocess.run([hipcc, *HIPCC_FLAGS, "--cuda-device-only", "-S", "-o", "-",
-                          os.path.join(CSRC, "pst_profile.hip")], check=True, capture_output=True,
-                         text=True).stdout
     h = hashlib.sha256()
-    inside = False
-    for line in asm.splitlines():
-        if re.match(r"^_Z\w*k_profile\w*:", line):
-            inside = True
-        if inside:
-            code = line.split(";")[0].rstrip()
-            if code and not code.lstrip().startswith("//"):
-                h.update(code.encode() + b"\n")
-            if line.startswith(".Lfunc_end"):
-                inside = False
+    for src in ("pst_stream.hip", "pst_profile.hip"):
+        asm = subprocess.run([hipcc, *HIPCC_FLAGS, "--cuda-device-only", "-S", "-o", "-",
+                              os.path.join(CSRC, src)], check=True, capture_output=True, text=True).stdout
+        inside = False
+        for line in asm.splitlines():
+            if re.match(r"^_Z\w*k_(profile|stream)\w*:", line):
+                inside = True
+            if inside:
+                code = line.split(";")[0].rstrip()
+                if code and not code.lstrip().startswith("//"):
+                    h.update(code.encode() + b"\n")
+                if line.startswith(".Lfunc_end"):
+                    inside = False
     return h.hexdigest()
 
 

@@ -49,6 +49,9 @@ namespace {
 
 using namespace pst;
 
+// words from a layout's max-D word to its tile counters (both in its 256 bytes)
+constexpr int kCounterAt = 4;
+
 size_t al(size_t v) { return (v + 255) & ~(size_t)255; }
 
 int fail(pst_ctx *c, int code, const char *fmt, ...) {
@@ -151,13 +154,14 @@ int series_stats(pst_ctx *c, const double *x, char *base, const StatsLayout &SL,
 }
 
 // Launch the profile kernel, bracketed by the context's events when timing.
-hipError_t timed_profile(pst_ctx *c, ProfileJob j) {
+// counter: kCounters zeroed words that hand out the work, or null.
+hipError_t timed_profile(pst_ctx *c, ProfileJob j, uint32_t *counter) {
     j.anchor_every = c->opt_anchor;
     if (c->timing) {
         hipError_t e = hipEventRecord(c->ev0, c->stream);
         if (e != hipSuccess) return e;
     }
-    hipError_t e = launch_profile(j, c->stream);
+    hipError_t e = launch_profile(j, counter, c->stream);
     if (e != hipSuccess) {
         fprintf(stderr, "pst: profile launch failed (w=%d grid=%d lds=%zu): %s\n", j.w, j.grid,
                 profile_lds_bytes(j.w), hipGetErrorString(e));
@@ -187,6 +191,7 @@ ProfileJob job_for(const Layout &L, char *ws, float *D, int64_t ld, unsigned *dm
     j.D = D;
     j.ld = ld;
     j.rw = (float *)(ws + L.o_rw);
+    j.rw_floats = (L.o_D - L.o_rw) / sizeof(float);
     j.dmax_bits = dmax_bits;
     j.grid = L.grid;
     return j;
@@ -218,9 +223,9 @@ int snippets_device(pst_ctx *c, const double *T, const Layout &L, char *ws, int3
     int rc = series_stats(c, T, ws + L.o_T, L.sT, "T");
     if (rc) return rc;
     unsigned *dmax = (unsigned *)(ws + L.o_dmax);
-    HIPCHK(c, launch_fill_u32(dmax, 1, 0u, c->stream));
+    HIPCHK(c, launch_fill_u32(dmax, kCounterAt + kCounters, 0u, c->stream));
     float *D = (float *)(ws + L.o_D);
-    HIPCHK(c, timed_profile(c, job_for(L, ws, D, L.Nm, dmax)));
+    HIPCHK(c, timed_profile(c, job_for(L, ws, D, L.Nm, dmax), dmax + kCounterAt));
     GreedyJob g = greedy_for(L, ws, D, L.Nm);
     g.owner = owner;
     g.profiles = profiles;
@@ -307,11 +312,12 @@ int run_multi(pst_ctx *c, const MultiPlan &P, const double *T, int64_t ldT, char
         HIPCHK(c, launch_fill_u32(dm, 1, 0u, c->stream));
         jobs[j] = job_for(L, region(j), (float *)(region(j) + L.o_D), L.Nm, dm);
         jobs[j].rw = (float *)(ws + P.o_rw);
+        jobs[j].rw_floats = (P.o_counter - P.o_rw) / sizeof(float);
         jobs[j].grid = P.grid;
         jobs[j].anchor_every = c->opt_anchor;
     }
     uint32_t *counter = (uint32_t *)(ws + P.o_counter);
-    HIPCHK(c, launch_fill_u32(counter, 1, 0u, c->stream));
+    HIPCHK(c, launch_fill_u32(counter, kCounters, 0u, c->stream));
     HIPCHK(c, profile_prepare(L.w));
     if (c->timing) HIPCHK(c, hipEventRecord(c->ev0, c->stream));
     HIPCHK(c, launch_profile_batch(jobs, P.d, P.grid, counter, c->stream));
@@ -375,7 +381,7 @@ int plan_blocked(pst_ctx *c, int64_t n, int32_t m, int32_t l, int32_t k, int32_t
     P->o_iota = o;   o = al(o + sizeof(int32_t) * K);
     P->o_dmax = o;   o = al(o + 256);
     P->o_crit = o;   o = al(o + sizeof(double) * (L.nblk2 + 1));
-    P->o_rw = o;     o = al(o + sizeof(float) * profile_scratch_bound(L.Nm, B, L.w));
+    P->o_rw = o;     o = al(o + sizeof(float) * profile_scratch_bound(L.Nm, B, L.w, false));
     P->total = o;
     return PST_OK;
 }
@@ -429,6 +435,7 @@ int run_blocked(pst_ctx *c, const BlockedLayout &P, const double *T, char *ws, p
     ProfileJob base = job_for(L, ws, Dblk, L.Nm, nullptr);
     base.col = st;
     base.rw = (float *)(ws + P.o_rw);
+    base.rw_floats = (P.total - P.o_rw) / sizeof(float);
     base.anchor_every = c->opt_anchor;
     for (int r = 0; r < L.K; ++r) {
         for (int32_t s0 = 0; s0 < L.nseg; s0 += P.B) {
@@ -441,7 +448,8 @@ int run_blocked(pst_ctx *c, const BlockedLayout &P, const double *T, char *ws, p
                 j.D = Dblk;
                 j.dmax_bits = r == 0 ? dmax : nullptr;
                 j.grid = profile_grid(L.ntile * (int64_t)nb, L.w);
-                HIPCHK(c, launch_profile_batch(&j, 1, j.grid, nullptr, c->stream));
+                HIPCHK(c, launch_fill_u32(dmax + kCounterAt, kCounters, 0u, c->stream));
+                HIPCHK(c, launch_profile_batch(&j, 1, j.grid, dmax + kCounterAt, c->stream));
                 if (D_host)
                     HIPCHK(c, hipMemcpyAsync(hblk, Dblk, sizeof(float) * (size_t)nb * L.Nm, hipMemcpyDeviceToHost,
                                              c->stream));
@@ -656,7 +664,7 @@ hipError_t launch_sweep_profiles(const SweepPlan &P, char *ws, int32_t grid, boo
     uint32_t *counter = (uint32_t *)(ws + P.o_counter);
     hipError_t e;
     if (one_launch) {  // every length in the widest one's geometry
-        if ((e = launch_fill_u32(counter, 1, 0u, st)) != hipSuccess) return e;
+        if ((e = launch_fill_u32(counter, kCounters, 0u, st)) != hipSuccess) return e;
         return launch_profile_batch(jobs, nj, grid, dynamic ? counter : nullptr, st);
     }
     int done = 0;
@@ -668,7 +676,7 @@ hipError_t launch_sweep_profiles(const SweepPlan &P, char *ws, int32_t grid, boo
         if (cnt == 0) continue;
         const int32_t g = std::max<int32_t>(1, (int32_t)((int64_t)profile_slots(wg) * grid / P.grid));
         for (int j = done; j < done + cnt; ++j) jobs[j].grid = g;
-        if ((e = launch_fill_u32(counter, 1, 0u, st)) != hipSuccess) return e;
+        if ((e = launch_fill_u32(counter, kCounters, 0u, st)) != hipSuccess) return e;
         if ((e = launch_profile_batch(jobs + done, cnt, g, dynamic ? counter : nullptr, st)) != hipSuccess) return e;
         done += cnt;
     }
@@ -1147,7 +1155,7 @@ int pst_mpdist_profile(pst_ctx *ctx, const double *T_dev, int64_t n, const doubl
     j.row_stride = 0;
     j.nq = 1;
     j.grid = profile_grid(L.ntile, L.w);
-    HIPCHK(ctx, timed_profile(ctx, j));
+    HIPCHK(ctx, timed_profile(ctx, j, nullptr));
     return PST_OK;
 }
 
@@ -1175,8 +1183,9 @@ int pst_mpdist_profile_noalloc(pst_ctx *ctx, const double *T_dev, int64_t n, con
     j.row_stride = 0;
     j.nq = 1;
     j.rw = (float *)(ws + used);
+    j.rw_floats = (cap - used) / sizeof(float);
     j.grid = (int32_t)std::min<int64_t>(profile_grid(L.ntile, L.w), (int64_t)((cap - used) / slot));
-    HIPCHK(ctx, timed_profile(ctx, j));
+    HIPCHK(ctx, timed_profile(ctx, j, nullptr));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return PST_OK;
 }
@@ -1193,8 +1202,8 @@ int pst_profile_set(pst_ctx *ctx, const double *T_dev, int64_t n, int32_t m, int
     char *ws = (char *)ws_dev;
     if ((rc = series_stats(ctx, T_dev, ws + L.o_T, L.sT, "T"))) return rc;
     unsigned *dmax = (unsigned *)(ws + L.o_dmax);
-    HIPCHK(ctx, launch_fill_u32(dmax, 1, 0u, ctx->stream));
-    HIPCHK(ctx, timed_profile(ctx, job_for(L, ws, D_dev, ld, dmax)));
+    HIPCHK(ctx, launch_fill_u32(dmax, kCounterAt + kCounters, 0u, ctx->stream));
+    HIPCHK(ctx, timed_profile(ctx, job_for(L, ws, D_dev, ld, dmax), dmax + kCounterAt));
     if (dmax_dev)
         HIPCHK(ctx, hipMemcpyAsync(dmax_dev, dmax, sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
     return PST_OK;

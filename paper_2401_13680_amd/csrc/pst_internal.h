@@ -52,12 +52,15 @@ struct ProfileJob {
     float *rw;             // scratch: profile_scratch_floats(grid, w) floats
     unsigned *dmax_bits;   // optional: atomic max of D's bit patterns
     int32_t grid;          // persistent workgroups
+    size_t rw_floats;      // floats at rw; 0: grid slots of the launch's geometry
     int32_t anchor_every;  // > 0: also re-anchor every diagonal at rows i % anchor_every == 0
 };
 // Up to kMaxJobs problems (for example every candidate m of a length sweep)
 // run in one persistent launch; tiles are striped over the workgroups, or
-// handed out by a device counter when `counter` is set (zeroed beforehand).
+// handed out by device counters when `counter` is set (kCounters words, zeroed
+// beforehand).
 constexpr int kMaxJobs = 16;
+constexpr int kCounters = 5;
 struct ProfileBatch {
     ProfileJob J[kMaxJobs];
     int64_t tile_end[kMaxJobs];   // job j owns tiles [tile_end[j-1], tile_end[j])
@@ -74,7 +77,7 @@ int32_t profile_slots(int32_t w);                 // profile workgroups resident
 int32_t profile_shape(int32_t w);                 // equal for w that get the same workgroup shape
 int32_t profile_grid(int64_t tiles, int32_t w);   // persistent grid for that many tiles
 size_t profile_scratch_floats(int32_t grid, int32_t w);
-hipError_t launch_profile(const ProfileJob &job, hipStream_t st);
+hipError_t launch_profile(const ProfileJob &job, uint32_t *counter, hipStream_t st);
 size_t profile_lds_bytes(int32_t w);   // dynamic LDS of one profile workgroup
 // Tile geometry of the profile kernel for w (workgroup size, diagonals per
 // thread, rows per chunk, selection threads, sub-tile width) as one code: the
@@ -85,8 +88,24 @@ size_t profile_lds_bytes(int32_t w);   // dynamic LDS of one profile workgroup
 int32_t profile_geometry(int32_t w);
 int32_t profile_geometry_candidates(int32_t w, int32_t *codes, int32_t max);
 bool profile_set_geometry(int32_t w, int32_t code);
-// Profile scratch floats that any candidate geometry needs for nq queries.
-size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w);
+// Profile scratch floats that any candidate geometry needs for nq queries;
+// with `full`, also what the streaming kernel uses when nothing limits it.
+size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true);
+
+// The streaming profile kernel (pst_stream.hip): whether it runs jobs of
+// width w in strips of SBW windows (`tile` of them to a tile), a workgroup's scratch and LDS for
+// a job of width w in a launch whose widest is wmax, the workgroups resident
+// at once, and the launches, one per kind of kernel the widths need (`share` of
+// the resident workgroups at most, as many as the scratch holds; kind k takes
+// counter[k], zeroed beforehand, when counter is set).
+constexpr int kStreamKinds = 4;
+bool stream_takes(int32_t w, int32_t SBW);
+size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);
+size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);
+int32_t stream_slots(int32_t w, int32_t SBW);
+hipError_t stream_prepare();
+hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
+                         double share, uint32_t *counter, hipStream_t st);
 
 // Greedy snippet search and its by-products, all on device (eqs. 6-8, 16-18).
 struct GreedyJob {

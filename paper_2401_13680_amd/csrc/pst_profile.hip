@@ -505,7 +505,7 @@ __device__ __forceinline__ float anchor_at(const ProfileJob &J, int64_t rb, int 
     const double *xcp = J.col.xc + C0 + u;
     double acc = 0.0;
     for (int tt = 0; tt < J.l; ++tt) acc = fma(xr[tt], xcp[tt], acc);
-    return (float)(acc - (double)J.l * J.row.mu[rb + i] * J.col.mu[C0 + u]);
+    return (float)fma(-((double)J.l * J.row.mu[rb + i]), J.col.mu[C0 + u], acc);
 }
 
 // FP64 anchors (centred covariance at the first cell) of a thread's V
@@ -550,8 +550,9 @@ __device__ __forceinline__ void diag_anchors(float (&cov)[V], const double *xr, 
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         const int d = d0 + v;
-        const double c = top ? acc[v] - (double)l * mur[0] * muc[ub0 + v]
-                             : acc[V - 1 - v] - (double)l * mur[base + V - 1 - v] * muc[0];
+        // (explicit: the streaming kernel must round alike)
+        const double c = top ? fma(-((double)l * mur[0]), muc[ub0 + v], acc[v])
+                             : fma(-((double)l * mur[base + V - 1 - v]), muc[0], acc[V - 1 - v]);
         if (d >= 0 && d < ndg) cov[v] = (float)c;
     }
 }
@@ -1293,7 +1294,7 @@ static size_t slot_floats_for(int32_t w) { return slot_floats_geo(w, geo_for(w))
 // The largest profile scratch any candidate geometry needs for nq queries of
 // Nm windows at w (workspaces are sized with it, so that a geometry chosen
 // later still fits).
-size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w) {
+size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full) {
     int32_t c[64];
     const int n = std::min(geo_candidates(w, c, 64), 64);
     size_t best = 0;
@@ -1304,7 +1305,13 @@ size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w) {
         best = std::max(best, (size_t)grid * slot_floats_geo(w, g));
     };
     for (int i = 0; i < n; ++i) one(geo_decode(c[i]));
-    one(geo_heuristic(w));
+    const Geo h = geo_heuristic(w);
+    one(h);
+    if (full && stream_takes(w, h.SBW)) {
+        const int64_t strips = ((Nm + h.SBW - 1) / h.SBW) * nq;
+        best = std::max(best, (size_t)std::min<int64_t>(strips, stream_slots(w, h.SBW)) *
+                                  stream_slot_floats(w, w, h.SBW));
+    }
     return best;
 }
 
@@ -1328,6 +1335,8 @@ static const void *kernel_for(const Geo &g) {
 hipError_t profile_prepare(int32_t wmax) {
     const Geo g = geo_for(wmax);
     const size_t lds = 4 * lds_floats(wmax, g);
+    const hipError_t e = stream_prepare();
+    if (e != hipSuccess) return e;
     return hipFuncSetAttribute(kernel_for(g), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
@@ -1337,28 +1346,49 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
     int wmax = 0;
     for (int i = 0; i < n; ++i) wmax = jobs[i].w > wmax ? jobs[i].w : wmax;
     const Geo g = geo_for(wmax);
+    if (!geometry_ok(wmax, g)) return hipErrorInvalidValue;
+    // The streaming kernel runs the jobs it takes where the launch has the
+    // built-in geometry; explicitly chosen geometries and re-anchoring inside
+    // the rows run k_profile.
+    const bool builtin = geo_code(g) == geo_code(geo_heuristic(wmax));
+    ProfileJob strips[kMaxJobs];
+    int ns = 0;
     ProfileArgs a;
     a.g = g;
-    a.B.njobs = n;
+    a.B.njobs = 0;
     a.B.slot_floats = slot_floats_for(wmax);
-    a.B.counter = counter;
+    a.B.counter = counter ? counter + kStreamKinds : nullptr;
     int64_t acc = 0;
     for (int i = 0; i < n; ++i) {
+        const bool anchored = jobs[i].anchor_every > 0;
+        if (builtin && !anchored && stream_takes(jobs[i].w, g.SBW)) {
+            strips[ns++] = jobs[i];
+            continue;
+        }
         // all jobs of a batch share the geometry of the widest one
-        a.B.J[i] = jobs[i];
+        const int j = a.B.njobs++;
+        a.B.J[j] = jobs[i];
         acc += ((jobs[i].Nm + g.JT - 1) / g.JT) * (int64_t)jobs[i].nq;
-        a.B.tile_end[i] = acc;
+        a.B.tile_end[j] = acc;
+    }
+    if (ns > 0) {
+        // a grid below the geometry's resident workgroups is the caller's limit
+        // where the scratch was sized by slots of that geometry
+        const bool sized = jobs[0].rw_floats > 0;
+        const size_t room = sized ? jobs[0].rw_floats : (size_t)grid * slot_floats_for(wmax);
+        const double share = sized ? 1.0 : std::min(1.0, (double)grid / profile_slots(wmax));
+        const hipError_t e = launch_stream(strips, ns, g.SBW, g.JT / g.SBW, room, share, counter, st);
+        if (e != hipSuccess || a.B.njobs == 0) return e;
     }
     const size_t lds = 4 * lds_floats(wmax, g);
-    if (!geometry_ok(wmax, g)) return hipErrorInvalidValue;
     void *args[] = {&a};
     return hipLaunchKernel(kernel_for(g), dim3(grid), dim3(g.NT), args, lds, st);
 }
 
-hipError_t launch_profile(const ProfileJob &job, hipStream_t st) {
+hipError_t launch_profile(const ProfileJob &job, uint32_t *counter, hipStream_t st) {
     hipError_t e = profile_prepare(job.w);
     if (e != hipSuccess) return e;
-    return launch_profile_batch(&job, 1, job.grid, nullptr, st);
+    return launch_profile_batch(&job, 1, job.grid, counter, st);
 }
 
 }  // namespace pst

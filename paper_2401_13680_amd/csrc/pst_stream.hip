@@ -1,0 +1,1215 @@
+// The streaming MPdist-profile kernel: eqs. 9-13 of section 4.1 for every
+// (query, window), with nothing of the distance matrix or of its sliding row
+// minima in global memory except the few rows that decide a window's value.
+//
+// A workgroup takes a strip: one query (w rows) against the SBW windows from
+// C0, i.e. the w x (SBW + w - 1) block of y = (1 - rho) / 2 in [0, 1] (see
+// pst_profile.hip: the same anchors, recurrence and clamp, cell for cell, so
+// the results are the same bits).  k-th smallest of a window's 2w values
+// (eq. 13) is found in two passes over the block:
+//
+//   1. Every thread owns V = 6 adjacent columns and walks down the rows; the
+//      covariance moves one column right per row (a wave shift).  Column
+//      minima (eq. 10) stay in registers; of the rows only the minima of
+//      groups of G columns are kept, in LDS.
+//   2. For each block of G windows: a row's sliding minimum (eq. 11) at every
+//      window of the block lies between the minimum over the groups that
+//      cover the block's windows (U) and the minimum over the whole groups
+//      inside all of them (C); a column minimum counts from the first window
+//      that holds it.  The k-th smallest U and the k-th smallest C bound the
+//      block's values: lo <= v <= hi, whatever the data.  Rows and columns
+//      with C < lo are below every v, those with U > hi above; the others
+//      (about a tenth of the rows) are listed.  In a third to a half of the
+//      blocks lo = hi and v is known.
+//   3. The rows are walked again and the listed (row, group) pieces of y are
+//      kept (global scratch, compact, so that most of it stays in L2).
+//   4. Each listed row's sliding minima over its block, one lane per row; then
+//      each window's selection among its block's listed values: a sorting
+//      network per window where the list is short, counts over the wave where
+//      it is long.
+//
+// Exact for any input: nothing is guessed that is not a bound.
+//
+// What bounds it: VALU issue.  At w = 129 (100 000 points, m = 256) the launch
+// takes 7.9 ms where k_profile takes 12.6: 44 vector instructions per 64 cells
+// (2 set-up and anchors, 8 first pass, 9 bounds, 5 second pass, 20 selection)
+// and 3.5 B of HBM traffic a cell, where k_profile moves 9.9 B a cell and is
+// held by that.
+//
+// A strip's windows reach w-1 columns into the next strip, and the column
+// minima there are the next strip's (k_profile's rule, except at the end of a
+// tile of 8 strips): a workgroup walks a run of strips right to left and keeps
+// those minima; before a run that ends inside a tile it walks the first w-1
+// columns of the strip to its right.
+#include "pst_internal.h"
+
+#include <algorithm>
+
+// A build with -DPST_PROBE adds up each wave's time between phase marks and a
+// few counts (pst_stream_probe_read); for analysis only.
+#ifdef PST_PROBE
+__device__ unsigned long long g_stream_probe[16 * 64];
+#define PROBE_ADD(i, c)                                                                             \
+    do {                                                                                            \
+        if ((threadIdx.x & 63) == 0)                                                                \
+            atomicAdd(&g_stream_probe[(i) * 64 + (blockIdx.x & 63)], (unsigned long long)(c));      \
+    } while (0)
+#define PROBE_MARK(v) const long long v = clock64()
+#define PROBE_SPAN(i, v) PROBE_ADD(i, clock64() - (v))
+#else
+#define PROBE_ADD(i, c) ((void)0)
+#define PROBE_MARK(v) ((void)0)
+#define PROBE_SPAN(i, v) ((void)0)
+#endif
+
+namespace pst {
+namespace {
+
+constexpr int V = 6;                 // columns per thread
+constexpr int VA = 7;                // diagonals per thread while anchoring
+constexpr int WCOL = 64 * V;         // columns of a wave
+constexpr int RCH = 6;               // rows per step of a pass
+constexpr int kMaxNT = 448;          // threads of the widest strip
+constexpr int KEYR = 18;             // keys per lane, at most: 2w + G - 1 <= 64 * KEYR
+constexpr int kSelect = 64 * 25;     // listed values that a wave holds in LDS
+constexpr int kSelectPad = 32 * 49;  // read past them, never used
+constexpr uint32_t kOne = 0x3F800000u;   // key of y = 1, the largest
+constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
+
+// Columns per group: about w/5, so that a block's bounds stay tight while the
+// group minima of a strip fit LDS.
+__host__ __device__ inline int stream_group(int w) { return w < 80 ? 12 : (w <= 180 ? 24 : 48); }
+
+struct StreamArgs {
+    ProfileBatch B;     // tile_end counts runs
+    int32_t SBW;
+    int32_t run;        // strips of a run, a divisor of `tile`
+    int32_t tile;       // strips of a tile
+};
+static_assert(sizeof(StreamArgs) <= 4000, "kernel arguments must fit the 4 KB limit");
+
+// Sizes of a strip of w rows in a workgroup of NT threads.
+struct Dims {
+    int NW, NC, NG, NGW, ldg, nblk, items, cap;
+    __host__ __device__ Dims(int G, int w, int NT, int SBW) {
+        NW = NT / 64;
+        NC = NT * V;                       // columns of the workgroup's threads
+        NG = (SBW + w - 1 + G - 1) / G;    // groups with columns of the strip
+        NGW = (NG + 31) / 32;              // mask words per row
+        ldg = (NG + 1) | 1;                // row stride of the group minima, one past the end (odd: lanes = rows)
+        nblk = (SBW + G - 1) / G;          // blocks of G windows
+        items = 2 * w + G - 1;             // rows and columns of a block's windows
+        cap = 64 * (G == 48 ? KEYR : G / 4);   // listed values a wave holds in scratch
+    }
+};
+
+// LDS of a strip, in floats.
+struct Lds {
+    int rst, bnd, col, carry, need, blk, bm, total, wp;
+    __host__ __device__ Lds(int G, int w, const Dims &d) {
+        wp = (w + RCH + 3) & ~3;
+        rst = 0;                                 // float4 [w]: {inv/2, df, dg, h/2}
+        bnd = rst + 4 * w;                       // [NW][wp] covariance left of each wave's columns
+        col = bnd + d.NW * wp;                   // [NC] anchors of row 0, then column minima
+        carry = col + d.NC;                      // [2][w] column minima of the strip to the right
+        need = (carry + 2 * w + 1) & ~1;         // uint2 [w][NGW]: groups to keep, slots before
+        blk = need + 2 * w * d.NGW;              // [nblk] {lo, hi, below, listed}
+        blk = (blk + 3) & ~3;
+        bm = blk + 4 * d.nblk;                   // [w][ldg] group minima; the anchors' staging before
+        const int lists = d.NW * kSelect + kSelectPad;   // later each wave's listed values
+        const int mins = (w * d.ldg + 3) & ~3;
+        total = bm + (mins > lists ? mins : lists);
+    }
+};
+
+// Scratch of one workgroup, in floats: the kept pieces of y, the lists, the
+// listed values of each wave.
+struct Scratch {
+    size_t pool, list, vals, total;
+    __host__ __device__ Scratch(int G, int w, const Dims &d) {
+        pool = 64;                                          // reads may start a value early
+        list = pool + (size_t)w * d.NG * G + 4 * G;             // and run past the last piece
+        list = (list + 63) & ~(size_t)63;
+        vals = list + 2 * (size_t)d.nblk * d.items;
+        vals = (vals + 63) & ~(size_t)63;
+        total = vals + (size_t)d.NW * d.cap * G;
+        total = (total + 63) & ~(size_t)63;
+    }
+};
+
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ __forceinline__ uint32_t key_of(float y) { return __float_as_uint(y); }
+__device__ __forceinline__ uint32_t bits(float y) { return __float_as_uint(y); }
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t x) {
+    return min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, CTRL, 0xf, 0xf, false));
+}
+// Sum over the wave of each lane's predicate.
+__device__ __forceinline__ int votes(bool p) { return __popcll(__ballot(p)); }
+// Smallest value of the wave (all lanes active), uniform.
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+    x = dpp_min<0xB1>(x);    // quad_perm [1,0,3,2]
+    x = dpp_min<0x4E>(x);    // quad_perm [2,3,0,1]
+    x = dpp_min<0x141>(x);   // row_half_mirror
+    x = dpp_min<0x140>(x);   // row_mirror
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) { return ~wave_min(~x); }
+
+__device__ __forceinline__ void exchange(uint32_t &a, uint32_t &b) {  // a <= b afterwards
+    const uint32_t x = a, y = b;
+    a = min(x, y);
+    b = max(x, y);
+}
+// Sorts a[0..N) ascending (Batcher's odd-even merge network, truncated to N).
+template <int N>
+__device__ __forceinline__ void sort_net(uint32_t (&a)[N]) {
+#pragma unroll
+    for (int p = 1; p < N; p += p) {
+#pragma unroll
+        for (int k = p; k > 0; k /= 2) {
+#pragma unroll
+            for (int j = k % p; j + k < N; j += 2 * k) {
+#pragma unroll
+                for (int i = 0; i < k; ++i) {
+                    if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) exchange(a[i + j], a[i + j + k]);
+                }
+            }
+        }
+    }
+}
+// a[i] for a lane's own 0 <= i < N: a tree of bit selects (an index would make
+// the wave loop over its lanes' values).
+template <int N>
+__device__ __forceinline__ uint32_t pick(const uint32_t (&a)[N], int i) {
+    uint32_t t[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = a[e];
+#pragma unroll
+    for (int d = 1; d < N; d *= 2) {
+        uint32_t odd = i & d ? 0xFFFFFFFFu : 0u;
+        asm("" : "+v"(odd));
+#pragma unroll
+        for (int e = 0; e < N; e += 2 * d)
+            if (e + d < N) t[e] = (t[e + d] & odd) | (t[e] & ~odd);
+    }
+    return t[0];
+}
+
+template <int NT_>
+__device__ __forceinline__ void stage_f64(double *dst, const double *src, int n, int t, int nt) {
+    constexpr int U = NT_;
+    for (int b = t; b < n; b += U * nt) {
+        double v[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) v[e] = b + e * nt < n ? src[b + e * nt] : 0.0;
+#pragma unroll
+        for (int e = 0; e < U; ++e)
+            if (b + e * nt < n) dst[b + e * nt] = v[e];
+    }
+}
+
+// FP64 anchors of a thread's VA diagonals d0 .. d0+VA-1 of a strip, as in
+// pst_profile.hip (the same sums in the same order): the covariance at the
+// first cell, (0, d-(w-1)) or (w-1-d, 0).
+__device__ __forceinline__ void anchors(float (&cov)[VA], const double *xr, const double *xc, int d0, int w, int l,
+                                        const double *mur, const double *muc) {
+    const int ub0 = d0 - (w - 1);
+    const bool top = ub0 >= 0;
+    const int base = -ub0 - (VA - 1);
+    const double *P = top ? xr : xc;
+    const double *Q = top ? xc + ub0 : xr + base;
+    double acc[VA], xs[VA];
+#pragma unroll
+    for (int v = 0; v < VA; ++v) acc[v] = 0.0;
+#pragma unroll
+    for (int v = 0; v < VA - 1; ++v) xs[v] = Q[v];
+    int tt = 0;
+    for (; tt + VA <= l; tt += VA) {
+#pragma unroll
+        for (int kq = 0; kq < VA; ++kq) {
+            xs[(kq + VA - 1) % VA] = Q[tt + kq + VA - 1];
+            const double a = P[tt + kq];
+#pragma unroll
+            for (int v = 0; v < VA; ++v) acc[v] = fma(a, xs[(kq + v) % VA], acc[v]);
+        }
+    }
+    for (; tt < l; ++tt) {
+        const double a = P[tt];
+#pragma unroll
+        for (int v = 0; v < VA; ++v) acc[v] = fma(a, Q[tt + v], acc[v]);
+    }
+#pragma unroll
+    for (int v = 0; v < VA; ++v) {
+        const double c = top ? fma(-((double)l * mur[0]), muc[ub0 + v], acc[v])
+                             : fma(-((double)l * mur[base + VA - 1 - v]), muc[0], acc[VA - 1 - v]);
+        cov[v] = (float)c;
+    }
+}
+
+// A thread's columns: statistics and the covariance at row 0.
+struct Cols {
+    float wi[V], wf[V], wg[V], wa[V], cov0[V];
+};
+
+// y of one row and the covariance of the next: cov moves one column right,
+// the wave's first lane takes the column left of it from `left`.
+template <bool CONST>
+__device__ __forceinline__ void row_step(const Cols &c, float (&cov)[V], const float4 &r, float left, uint32_t (&y)[V],
+                                         float &last) {
+    float nx[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const float a = CONST ? c.wa[v] - r.w : c.wa[v];
+        y[v] = key_of(__builtin_amdgcn_fmed3f(fmaf(-cov[v] * r.x, c.wi[v], a), 0.0f, 1.0f));
+        nx[v] = fmaf(r.y, c.wg[v], fmaf(c.wf[v], r.z, cov[v]));
+    }
+    last = nx[V - 1];
+#pragma unroll
+    for (int v = V - 1; v > 0; --v) cov[v] = nx[v - 1];
+    // wave_shr:1
+    cov[0] = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(left), __float_as_int(last), 0x138, 0xf, 0xf,
+                                                        false));
+}
+
+// Minimum of a row over the group of G columns a lane belongs to.
+template <int G>
+__device__ __forceinline__ uint32_t group_min(const uint32_t (&y)[V]) {
+    uint32_t m = min(min(min(y[0], y[1]), y[2]), min(min(y[3], y[4]), y[5]));
+    m = dpp_min<0xB1>(m);                // quad_perm [1,0,3,2]
+    if (G >= 24) m = dpp_min<0x4E>(m);   // quad_perm [2,3,0,1]
+    if (G >= 48) m = dpp_min<0x141>(m);  // row_half_mirror
+    return m;
+}
+
+// First pass: column minima into colmin, group minima into bm, the covariance
+// left of each wave into bnd.  Wave k runs a step behind wave k-1.
+template <int G, bool CONST>
+__device__ __forceinline__ void pass_one(const Cols &c, uint32_t (&colmin)[V], const float4 *rst, float *bnd, int wp,
+                                         uint32_t *bm, int ldg, int NG, int w, int nwa, int wv,
+                                         int lane) {
+    const int nch = (w + RCH - 1) / RCH;
+    const int g = (wv * 64 + lane) / (G / V);
+    const bool lead = lane % (G / V) == 0 && g < NG;
+    const float *lb = bnd + wv * wp;
+    float *rb = bnd + (wv + 1) * wp;
+    float cov[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        cov[v] = c.cov0[v];
+        colmin[v] = kOne;
+    }
+    for (int s = 0; s < nch + nwa - 1; ++s) {
+        const int ch = s - wv;
+        if (wv < nwa && ch >= 0 && ch < nch) {
+            const int r0 = ch * RCH;
+            if (r0 + RCH <= w) {
+                float4 rr[RCH];
+                float lf[RCH], out[RCH];
+                uint32_t mg[RCH];
+#pragma unroll
+                for (int e = 0; e < RCH; ++e) {
+                    rr[e] = rst[r0 + e];
+                    lf[e] = lb[r0 + e + 1];
+                }
+#pragma unroll
+                for (int e = 0; e < RCH; e += 2) {
+                    uint32_t y0[V], y1[V];
+                    row_step<CONST>(c, cov, rr[e], lf[e], y0, out[e]);
+                    row_step<CONST>(c, cov, rr[e + 1], lf[e + 1], y1, out[e + 1]);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) colmin[v] = min(min(colmin[v], y0[v]), y1[v]);
+                    mg[e] = group_min<G>(y0);
+                    mg[e + 1] = group_min<G>(y1);
+                }
+                if (lead) {
+#pragma unroll
+                    for (int e = 0; e < RCH; ++e) bm[(r0 + e) * ldg + g] = mg[e];
+                }
+                if (lane == 63 && wv + 1 < nwa) {
+#pragma unroll
+                    for (int e = 0; e < RCH; ++e) rb[r0 + e + 1] = out[e];
+                }
+            } else {
+                for (int i = r0; i < w; ++i) {
+                    uint32_t y[V];
+                    float out;
+                    row_step<CONST>(c, cov, rst[i], lb[i + 1], y, out);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) colmin[v] = min(colmin[v], y[v]);
+                    const uint32_t m = group_min<G>(y);
+                    if (lead) bm[i * ldg + g] = m;
+                    if (lane == 63 && wv + 1 < nwa) rb[i + 1] = out;
+                }
+            }
+        }
+        lds_barrier();
+    }
+}
+
+// Second pass: the pieces of y named in need (this wave's mask word of each
+// row and the slots before it) into the pool.
+template <int G, bool CONST>
+__device__ __forceinline__ void pass_two(const Cols &c, const float4 *rst, const float *lb, const uint2 *need, int ngw,
+                                         int NG, float *pool, int w, int t) {
+    const int g = t / (G / V);
+    const uint32_t bit = g < NG ? 1u << (g & 31) : 0u;
+    const uint2 *nd = need + uni(min(g >> 5, ngw - 1));
+    float *mine = pool + (t % (G / V)) * V;
+    float cov[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) cov[v] = c.cov0[v];
+    auto keep = [&](const uint32_t (&y)[V], const uint2 &q) {
+        if (q.x & bit) {
+            float2 *p = (float2 *)(mine + (size_t)(q.y + __popc(q.x & (bit - 1u))) * G);
+            p[0] = make_float2(__uint_as_float(y[0]), __uint_as_float(y[1]));
+            p[1] = make_float2(__uint_as_float(y[2]), __uint_as_float(y[3]));
+            p[2] = make_float2(__uint_as_float(y[4]), __uint_as_float(y[5]));
+        }
+    };
+    int i = 0;
+    for (; i + RCH <= w; i += RCH) {
+        float4 rr[RCH];
+        float lf[RCH];
+        uint2 q[RCH];
+#pragma unroll
+        for (int e = 0; e < RCH; ++e) {
+            rr[e] = rst[i + e];
+            lf[e] = lb[i + e + 1];
+            q[e] = nd[(i + e) * ngw];
+        }
+#pragma unroll
+        for (int e = 0; e < RCH; ++e) {
+            uint32_t y[V];
+            float out;
+            row_step<CONST>(c, cov, rr[e], lf[e], y, out);
+            keep(y, q[e]);
+        }
+    }
+    for (; i < w; ++i) {
+        uint32_t y[V];
+        float out;
+        row_step<CONST>(c, cov, rst[i], lb[i + 1], y, out);
+        keep(y, nd[i * ngw]);
+    }
+}
+
+// Keys of the wave that are at most x.
+template <int NR>
+__device__ __forceinline__ int count_le(const uint32_t (&K)[NR], uint32_t x) {
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) n += votes(K[r] <= x);
+    return n;
+}
+// The smallest key above x (signed: -1 is below every key), and the largest
+// that is at most x.
+template <int NR>
+__device__ __forceinline__ uint32_t next_above(const uint32_t (&K)[NR], int x) {
+    uint32_t m = kNone;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) m = min(m, (int)(K[r] & 0x7FFFFFFFu) > x ? K[r] : kNone);
+    return wave_min(m);
+}
+template <int NR>
+__device__ __forceinline__ uint32_t last_at(const uint32_t (&K)[NR], uint32_t x) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) m = max(m, K[r] <= x ? K[r] : 0u);
+    return wave_max(m);
+}
+
+// A point strictly inside (xl, xh), xh - xl > 1, aimed at rank k between the
+// counts cl < k <= ch: interpolated, every third time the middle.
+__device__ __forceinline__ int aim(int xl, int xh, int cl, int ch, int k, int it) {
+    const float d = (float)(xh - xl);
+    const float f = it % 3 == 2 ? 0.5f : ((float)(k - cl) - 0.5f) * __builtin_amdgcn_rcpf((float)(ch - cl));
+    return min(max(uni(xl + (int)(d * f)), xl + 1), xh - 1);
+}
+
+// The k-th smallest of the wave's keys, which lies in (xl, xh] with cl < k
+// keys at most xl and ch >= k at most xh.  With slack >= 0 any x at or above it
+// that has at most k + slack keys at or below it will do.
+template <int NR>
+__device__ __forceinline__ uint32_t find_rank(const uint32_t (&K)[NR], int k, int xl, int cl, int xh, int ch,
+                                              int slack) {
+    for (int it = 0;; ++it) {
+        if (slack >= 0 && ch <= k + slack) return (uint32_t)xh;
+        if (cl == k - 1 || xh - xl <= 1) return next_above<NR>(K, xl);
+        if (ch == k) return last_at<NR>(K, (uint32_t)xh);
+        const int x = aim(xl, xh, cl, ch, k, it);
+        const int c = count_le<NR>(K, (uint32_t)x);
+        if (c >= k) {
+            xh = x;
+            ch = c;
+        } else {
+            xl = x;
+            cl = c;
+        }
+    }
+}
+
+// The same from a guess x and the spacing of the keys around it: steps that
+// double until rank k is bracketed.
+template <int NR>
+__device__ __forceinline__ uint32_t find_from(const uint32_t (&K)[NR], int k, int x, int step, int xl, int cl, int top,
+                                              int slack) {
+    int xh = top, ch = 64 * NR;
+    x = min(max(x, xl + 1), xh - 1);
+    while (x > xl && x < xh) {
+        const int c = count_le<NR>(K, (uint32_t)x);
+        if (c >= k) {
+            xh = x;
+            ch = c;
+            if (slack >= 0 && ch <= k + slack) return (uint32_t)xh;
+            if (cl == k - 1 || ch == k) break;
+            if (xl >= 0) break;
+            x -= min(step * (c - k + 1), x);   // 0 at the least
+        } else {
+            xl = x;
+            cl = c;
+            if (cl == k - 1 || ch != 64 * NR) break;
+            x += min(step * (k - c), (int)kOne);
+        }
+        step = min(step * 2, 1 << 20);
+    }
+    if (ch == 64 * NR) ch = count_le<NR>(K, (uint32_t)xh);
+    if (ch < k) return (uint32_t)top;    // fewer than k keys: the largest y there is
+    return find_rank<NR>(K, k, xl, cl, xh, ch, slack);
+}
+
+// U and C of this lane's rows for block a: the groups a .. a + GC + GE hold the
+// columns of the block's windows, a+1 .. a+GC lie inside every one of them.
+template <int NR, int GC, int GE>
+__device__ __forceinline__ void row_keys(uint32_t (&U)[NR], uint32_t (&C)[NR], const uint32_t *bm, int ldg, int w, int a,
+                                         int lane) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        U[r] = kNone;
+        C[r] = kNone;
+        if (64 * r < w) {
+            const int x = lane + 64 * r;
+            if (x < w) {
+                const uint32_t *row = bm + x * ldg + a;
+                uint32_t m[GC + GE + 1];
+#pragma unroll
+                for (int q = 0; q <= GC + GE; ++q) m[q] = row[q];
+                uint32_t c = m[1];
+#pragma unroll
+                for (int q = 2; q <= GC; ++q) c = min(c, m[q]);
+                uint32_t u = min(c, m[0]);
+#pragma unroll
+                for (int q = GC + 1; q <= GC + GE; ++q) u = min(u, m[q]);
+                U[r] = u;
+                C[r] = c;
+            }
+        }
+    }
+}
+template <int NR, int GC0, int GC1>
+__device__ __forceinline__ void row_keys_of(uint32_t (&U)[NR], uint32_t (&C)[NR], const uint32_t *bm, int ldg, int w,
+                                            int a, int lane, int gc, int ge) {
+    if constexpr (GC0 < GC1) {
+        if (gc > GC0) {
+            row_keys_of<NR, GC0 + 1, GC1>(U, C, bm, ldg, w, a, lane, gc, ge);
+            return;
+        }
+    }
+    if (ge <= 1) row_keys<NR, GC0, 1>(U, C, bm, ldg, w, a, lane);
+    else row_keys<NR, GC0, 2>(U, C, bm, ldg, w, a, lane);
+}
+
+// Bounds and lists of the blocks [a0, a1) of a strip, by one wave; lane + 64 r
+// is row i < w or column x - w of the block's columns.  GC0 .. GC1: the whole
+// groups inside a block's windows.
+template <int G, int NR, int GC0, int GC1>
+__device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int CS, const Dims &d, const uint32_t *bm,
+                                             const uint32_t *colk, uint32_t *need, uint4 *blk, uint2 *list, int lane) {
+    const int gc = w / G - 1;                 // groups a+1 .. a+gc lie inside every window of the block
+    const int ge = 1 + (w - 2) / G - gc;      // groups past them that hold a column of its windows
+    const int rem = w % G;
+    uint32_t U[NR], C[NR];
+    uint32_t lo = 0x3D800000u, hi = lo;       // guesses: y = 1/16, then the block before
+    for (int a = a0; a < a1; ++a) {
+        row_keys_of<NR, GC0, GC1>(U, C, bm, d.ldg, w, a, lane, gc, ge);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (64 * r + 63 >= w) {
+                const int cx = lane + 64 * r - w, cg = a * G + cx;
+                if (cx >= 0 && cx < w + G - 1 && cg < CS) {
+                    const uint32_t u = colk[cg];
+                    U[r] = u;
+                    C[r] = cx >= G - 1 && cx < w ? u : kNone;
+                }
+            }
+        }
+    // lo: the k-th smallest U; hi: no less than the k-th smallest C
+        const int span = max((int)(hi - lo), 1 << 10);
+        lo = find_from<NR>(U, k, (int)lo, min(max(span / 8, 1 << 10), 1 << 20), -1, 0, (int)kOne, -1);
+        const int ce = count_le<NR>(C, lo);
+        if (ce >= k) {
+            if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
+            hi = lo;
+            continue;
+        }
+        hi = lo >= kOne ? kOne
+                        : find_from<NR>(C, k, (int)max(hi, lo + (uint32_t)span / 2), min(max(span / 8, 1 << 10), 1 << 20), (int)lo, ce,
+                                        (int)kOne, 2 + (k >> 4));
+        // below lo everywhere; listed: the rest that may be at most hi
+        int below = 0, n = 0;
+        uint2 *la = list + (size_t)a * d.items;
+        const int gr = a + w / G;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int x = lane + 64 * r;
+            const bool b = C[r] < lo;
+            const bool in = !b && U[r] <= hi;
+            below += votes(b);
+            const uint64_t m = __ballot(in);
+            if (m == 0) continue;
+            if (in) {
+                const int pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                const bool isrow = x < w;
+                la[pos] = make_uint2(isrow ? (uint32_t)x : 0x80000000u | (uint32_t)(x - w), isrow ? C[r] : U[r]);
+                if (64 * r < w && isrow) {
+                    uint32_t *nd = need + 2 * (x * d.NGW);
+                    atomicOr(nd + 2 * (a >> 5), 1u << (a & 31));
+                    if (gr < d.NG) atomicOr(nd + 2 * (gr >> 5), 1u << (gr & 31));
+                    if (rem >= 2 && gr + 1 < d.NG) atomicOr(nd + 2 * ((gr + 1) >> 5), 1u << ((gr + 1) & 31));
+                }
+            }
+            n += __popcll(m);
+        }
+        if (lane == 0) blk[a] = make_uint4(lo, hi, (uint32_t)below, (uint32_t)n);
+    }
+}
+
+// block_bounds with the registers that w needs.
+template <int G, int KR>
+__device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int CS, const Dims &d, const uint32_t *bm,
+                                             const uint32_t *colk, uint32_t *need, uint4 *blk, uint2 *list, int lane) {
+    const int nr = (d.items + 63) / 64;
+#define BOUNDS(NR, GC0, GC1) block_bounds<G, NR, GC0, GC1>(a0, a1, w, k, CS, d, bm, colk, need, blk, list, lane)
+    // the widths of each kind: see stream_group and kKindR
+    if constexpr (G == 12) {
+        if (nr <= 2) BOUNDS(2, 1, 4);
+        else BOUNDS(3, 3, 5);
+    } else if constexpr (G == 24) {
+        if (nr <= 4) BOUNDS(4, 2, 3);
+        else if (nr == 5) BOUNDS(5, 3, 5);
+        else BOUNDS(6, 4, 6);
+    } else if constexpr (KR <= 9) {
+        BOUNDS(9, 2, 4);
+    } else {
+        if (nr <= 13) BOUNDS(13, 4, 7);
+        else BOUNDS(18, 6, 10);
+    }
+#undef BOUNDS
+}
+
+// One listed item of block a over the block's G windows, by one lane.
+template <int G>
+__device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &d, const uint2 *need,
+                                            const float *pool, uint32_t (&o)[G]) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef f4 f4u __attribute__((aligned(4)));
+    if (it.x & 0x80000000u) {  // a column: in the windows that hold it
+        const int cx = (int)(it.x & 0x7FFFFFFFu);
+#pragma unroll
+        for (int p = 0; p < G; ++p) o[p] = (p <= cx && p >= cx - w + 1) ? it.y : kNone;
+    } else {
+        // a row: suffix minima of its group, the whole groups inside (it.y),
+        // and running minima of the columns that follow
+        const uint2 *nd = need + (int)it.x * d.NGW;
+        auto slot = [&](int g) {
+            const uint2 q = nd[min(g >> 5, d.NGW - 1)];
+            return (int)(q.y + __popc(q.x & ((1u << (g & 31)) - 1u)));
+        };
+        const float *pa = pool + (size_t)slot(a) * G;
+        const int rem = w % G;
+        const float *pr = pool + (size_t)slot(a + w / G) * G;
+        const float *pt = pr + rem - 1;
+#pragma unroll
+        for (int p = 0; p < G; p += 4) {
+            const f4 q = *(const f4 *)(pa + p);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[p + e] = bits(q[e]);
+        }
+        uint32_t run = it.y;
+        for (int x = 0; x < rem - 1; x += 4) {  // columns 0 .. rem-2 (those past it repeat nothing)
+            const f4 q = *(const f4 *)(pr + x);
+            run = min(run, bits(q[0]));
+#pragma unroll
+            for (int e = 1; e < 4; ++e) run = min(run, x + e < rem - 1 ? bits(q[e]) : kNone);
+        }
+#pragma unroll
+        for (int p = G - 2; p >= 0; --p) o[p] = min(o[p], o[p + 1]);
+        constexpr int H = G < 24 ? G : 24;   // loads in flight
+#pragma unroll
+        for (int h = 0; h < G; h += H) {
+            f4 t[H / 4];
+#pragma unroll
+            for (int p = 0; p < H / 4; ++p) t[p] = *(const f4u *)(pt + h + 4 * p);
+#pragma unroll
+            for (int p = 0; p < H; ++p) {
+                const uint32_t y = h + p == 0 && rem == 0 ? kNone : bits(t[p / 4][p % 4]);
+                run = min(run, y);
+                o[h + p] = min(o[h + p], run);
+            }
+            if (G > H) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// The kk-th smallest of a window's n <= N listed values, v[e * st] in LDS.
+template <int N, int ST>
+__device__ __forceinline__ uint32_t select_sorted(const uint32_t *v, int n, int kk) {
+    uint32_t c[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = v[e * ST];
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = e < n ? c[e] : kNone;
+    sort_net(c);
+    return pick(c, kk - 1);
+}
+
+// As select_sorted for n <= 64 values shared by the lanes p and p + 32: each
+// sorts every second one; the 32 smallest of the two lists (or, past rank 32,
+// the 32 largest) are the minima (maxima) of one list against the other's
+// reverse, and a bitonic merge sorts them.
+template <int ST>
+__device__ __forceinline__ uint32_t select_halved(const uint32_t *v, int n, int kk, int half) {
+    uint32_t c[32], z[32];
+    const uint32_t *vh = v + half * ST;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) c[e] = vh[2 * e * ST];
+#pragma unroll
+    for (int e = 0; e < 32; ++e) c[e] = 2 * e + half < n ? c[e] : kNone;
+    sort_net(c);
+    const bool upper = kk > 32;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+        const uint32_t o = (uint32_t)__shfl_xor((int)c[31 - e], 32);
+        z[e] = upper ? max(c[e], o) : min(c[e], o);
+    }
+#pragma unroll
+    for (int d = 16; d > 0; d /= 2) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e)
+            if (!(e & d)) exchange(z[e], z[e + d]);
+    }
+    return pick(z, upper ? kk - 33 : kk - 1);
+}
+
+// The kk-th smallest of the wave's n keys: v is a first guess, lo and hi are
+// bounds.  A window's value is mostly the one before it or a neighbour in
+// rank: two counts, or one reduction more.
+template <int NR>
+__device__ __forceinline__ uint32_t settle(const uint32_t (&X)[NR], int n, int kk, uint32_t v, uint32_t lo,
+                                           uint32_t hi) {
+    const int le = count_le<NR>(X, v);
+    if (le < kk) {
+        if (le == kk - 1) return next_above<NR>(X, (int)v);
+        return find_rank<NR>(X, kk, (int)v, le, (int)hi, n, -1);
+    }
+    int lt = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) lt += votes(X[r] < v);
+    if (lt < kk) return v;
+    if (lt == kk) return last_at<NR>(X, v - 1u);
+    return find_rank<NR>(X, kk, (int)lo - 1, 0, (int)v - 1, lt, -1);
+}
+
+// The values of np windows whose nr * 64 listed values lie at vals[p * 64 nr];
+// lane p of the result is window p.
+template <int NR>
+__device__ __forceinline__ uint32_t select_windows(const uint32_t *vals, int np, int n, int kk, uint32_t &v,
+                                                   uint32_t lo, uint32_t hi, int lane) {
+    uint32_t res = 0u;
+    uint32_t x[NR], nx[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) nx[r] = vals[64 * r + lane];
+    for (int p = 0; p < np; ++p) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) x[r] = nx[r];
+        const uint32_t *next = vals + min(p + 1, np - 1) * (64 * NR) + lane;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) nx[r] = next[64 * r];
+        v = settle<NR>(x, n, kk, v, lo, hi);
+        res = lane == p ? v : res;
+    }
+    return res;
+}
+
+struct Strip {
+    const ProfileJob *J;
+    int s, CS, JSe;     // JSe = 0: only the column minima, for the strip to the left
+    int64_t C0;
+    const uint32_t *in; // minima of the columns past SBW, from the strip to the right, or null
+    uint32_t *out;      // minima of the first w-1 columns, for the strip to the left
+};
+
+template <int G, int KR>
+__device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr, int NT, int SBW, float &tmax) {
+    const ProfileJob &J = *S.J;
+    // opaque to the compiler, so that nothing computed from them is kept in
+    // registers from one strip to the next
+    int w = J.w, t = threadIdx.x;
+    asm volatile("" : "+s"(w), "+s"(NT), "+s"(SBW), "+v"(t));
+    const int l = J.l;
+    const Dims d(G, w, NT, SBW);
+    const Lds L(G, w, d);
+    const Scratch X(G, w, d);
+    const int wv = uni(t >> 6), lane = t & 63;
+    const int64_t rb = (int64_t)S.s * J.row_stride;
+    float4 *rst = (float4 *)(sm + L.rst);
+    float *bnd = sm + L.bnd;
+    float *col = sm + L.col;
+    uint32_t *need = (uint32_t *)(sm + L.need);
+    uint4 *blk = (uint4 *)(sm + L.blk);
+    uint32_t *bm = (uint32_t *)(sm + L.bm);
+    const int CS = S.CS;
+    const int nwa = (CS + WCOL - 1) / WCOL;   // waves with columns
+
+    PROBE_MARK(t0);
+    // row statistics; the anchors' slices of the centred series
+    int crow = 0;
+    for (int i = t; i < w; i += NT) {
+        const int64_t r = rb + i;
+        const float hr = J.row.h[r];
+        rst[i] = make_float4(0.5f * J.row.inv[r], J.row.df[r], J.row.dg[r], 0.5f * hr);
+        crow |= hr != 0.0f;
+    }
+    for (int i = t; i < w * d.NGW; i += NT) need[2 * i] = 0u;
+    for (int i = CS + t; i < d.NC; i += NT) col[i] = 0.0f;
+    const int ndg = CS + w - 1;
+    const int off = (VA - (w - 1) % VA) % VA;
+    const int ncx = CS + VA + l, nrx = w + l + VA - 2;
+    const bool staged = 2 * (ncx + nrx) <= L.total - L.bm;
+    double *Xc = (double *)bm, *Xr = Xc + ncx;
+    if (staged) {
+        stage_f64<4>(Xc, J.col.xc + S.C0, ncx, t, NT);
+        stage_f64<4>(Xr, J.row.xc + rb, nrx, t, NT);
+    }
+    const bool any_const = __syncthreads_or(crow) != 0;
+    const int d0 = t * VA - off;
+    if (d0 < ndg) {
+        float a[VA];
+        if (staged) anchors(a, Xr, Xc, d0, w, l, J.row.mu + rb, J.col.mu + S.C0);
+        else anchors(a, J.row.xc + rb, J.col.xc + S.C0, d0, w, l, J.row.mu + rb, J.col.mu + S.C0);
+#pragma unroll
+        for (int v = 0; v < VA; ++v) {
+            const int q = d0 + v;
+            if (q >= 0 && q < ndg) {
+                if (q >= w - 1) col[q - (w - 1)] = a[v];
+                else bnd[w - 1 - q] = a[v];
+            }
+        }
+    }
+    Cols c;
+    const int u0 = t * V;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int u = u0 + v;
+        const bool in = u < CS;
+        const int64_t cc = S.C0 + (in ? u : 0);
+        // outside the strip: y = 1, neutral for every minimum
+        c.wi[v] = in ? J.col.inv[cc] : 0.0f;
+        c.wf[v] = in ? J.col.df[cc] : 0.0f;
+        c.wg[v] = in ? J.col.dg[cc] : 0.0f;
+        c.wa[v] = in ? 0.5f - 0.5f * J.col.h[cc] : 2.0f;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int v = 0; v < V; ++v) c.cov0[v] = col[u0 + v];
+    uint32_t colmin[V];
+    PROBE_SPAN(0, t0);
+    PROBE_MARK(t1);
+    if (any_const)
+        pass_one<G, true>(c, colmin, rst, bnd, L.wp, bm, d.ldg, d.NG, w, nwa, wv, lane);
+    else
+        pass_one<G, false>(c, colmin, rst, bnd, L.wp, bm, d.ldg, d.NG, w, nwa, wv, lane);
+    uint32_t *colk = (uint32_t *)col;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int u = u0 + v;
+        if (u < w - 1) S.out[u] = colmin[v];
+        colk[u] = S.in && u >= SBW && u < CS ? S.in[u - SBW] : colmin[v];
+    }
+    PROBE_SPAN(1, t1);
+    if (S.JSe == 0) return;
+    // groups past the last active wave hold nothing
+    for (int i = t; i < w; i += NT)
+        for (int g = min(nwa * (WCOL / G), d.NG); g <= d.NG; ++g) bm[i * d.ldg + g] = kOne;
+    lds_barrier();
+
+    float *pool = scr + X.pool;
+    uint2 *list = (uint2 *)(scr + X.list);
+    const int nblk = (S.JSe + G - 1) / G;
+    const int per = (nblk + d.NW - 1) / d.NW;
+    PROBE_MARK(t2);
+    strip_bounds<G, KR>(min(wv * per, nblk), min(wv * per + per, nblk), w, min(J.k, 2 * w), CS, d, bm, colk, need, blk,
+                    list, lane);
+    PROBE_SPAN(2, t2);
+    __syncthreads();
+    PROBE_SPAN(3, t2);
+    PROBE_MARK(t3);
+    // slots of the kept pieces, in (row, group) order
+    const uint2 *need2 = (const uint2 *)need;
+    if (wv == 0) {
+        const int tot = w * d.NGW, pl = (tot + 63) / 64;
+        const int b = lane * pl, e = min(b + pl, tot);
+        int sum = 0;
+        for (int i = b; i < e; ++i) sum += __popc(need[2 * i]);
+        int inc = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+        int at = inc - sum;
+        for (int i = b; i < e; ++i) {
+            need[2 * i + 1] = (uint32_t)at;
+            at += __popc(need[2 * i]);
+        }
+    }
+    lds_barrier();
+    if (wv < nwa) {
+        const float *lb = bnd + wv * L.wp;
+        if (any_const)
+            pass_two<G, true>(c, rst, lb, need2, d.NGW, d.NG, pool, w, t);
+        else
+            pass_two<G, false>(c, rst, lb, need2, d.NGW, d.NG, pool, w, t);
+    }
+    __syncthreads();
+    PROBE_SPAN(4, t3);
+    PROBE_MARK(t4);
+
+    // selection: one lane per listed item for its values over its block, then
+    // one lane per window
+    const int keff = min(J.k, 2 * w);
+    const float four_l = (float)(4 * l);
+    uint32_t *lvals = bm + wv * kSelect;   // the group minima are done with
+    const int ab = min(wv * per, nblk), ae = min(wv * per + per, nblk);
+    auto put = [&](int a, int p, bool on, uint32_t y) {
+        if (on) {
+            const float dist = sqrtf(four_l * __uint_as_float(y));
+            J.D[(int64_t)S.s * J.ld + S.C0 + a * G + p] = dist;
+            tmax = fmaxf(tmax, dist);
+        }
+    };
+    auto wave_sync = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    // blocks of up to 32 items are taken several at a time, as many as their
+    // items and windows fit the lanes
+    constexpr int LB = G == 12 ? 16 : (G == 24 ? 32 : 64), NB = 64 / LB, ST = G + 1;
+    int cnt = 0, T = 0, nmax = 0;
+    int mya = 0, myb = 0;   // of the lane's window: its block, the block's first item
+    int ita = 0, itb = 0;   // of the lane's item
+    for (int a = ab;; ++a) {
+        const bool end = a >= ae;
+        const uint4 bl = blk[end ? ab : a];
+        const int n0 = end ? 0 : uni((int)bl.w);
+        const bool few = n0 > 0 && n0 <= 32;
+        if (cnt > 0 && (end || (few && (cnt == NB || T + n0 > 64)))) {
+            PROBE_MARK(t5);
+            PROBE_ADD(8, cnt);
+            PROBE_ADD(9, T);
+            if (lane < T) {
+                uint32_t o[G];
+                item_values<G>(list[(size_t)ita * d.items + (lane - itb)], ita, w, d, need2, pool, o);
+#pragma unroll
+                for (int p = 0; p < G; ++p) lvals[lane * ST + p] = o[p];
+            }
+            wave_sync();
+            PROBE_SPAN(6, t5);
+            const int p = lane % LB;
+            const bool on = lane / LB < cnt && p < G && p < S.JSe - mya * G;
+            const uint4 mb = blk[mya];
+            const int n = on ? (int)mb.w : 0;
+            const uint32_t *v = lvals + (on ? myb * ST + p : 0);
+            const int kk = keff - (int)mb.z;
+            uint32_t r;
+            if (nmax <= 8) r = select_sorted<8, ST>(v, n, kk);
+            else if (nmax <= 12) r = select_sorted<12, ST>(v, n, kk);
+            else if (nmax <= 16) r = select_sorted<16, ST>(v, n, kk);
+            else if (nmax <= 20) r = select_sorted<20, ST>(v, n, kk);
+            else if (nmax <= 26) r = select_sorted<26, ST>(v, n, kk);
+            else r = select_sorted<32, ST>(v, n, kk);
+            put(mya, p, on, r);
+            wave_sync();
+            cnt = T = nmax = 0;
+        }
+        if (end) break;
+        const int np = min(G, S.JSe - a * G);
+        if (n0 == 0) {
+            put(a, lane, lane < np, bl.x);
+        } else if (few) {
+            if (lane / LB >= cnt) {
+                mya = a;
+                myb = T;
+            }
+            if (lane >= T) {
+                ita = a;
+                itb = T;
+            }
+            ++cnt;
+            T += n0;
+            nmax = max(nmax, n0);
+        } else if (n0 <= 64) {
+            constexpr int HW = G < 24 ? G : 24, SH = HW + 1;
+            PROBE_MARK(t5);
+            PROBE_ADD(8, 1);
+            PROBE_ADD(9, n0);
+            uint32_t o[G];
+            item_values<G>(list[(size_t)a * d.items + min(lane, n0 - 1)], a, w, d, need2, pool, o);
+            PROBE_SPAN(6, t5);
+#pragma unroll
+            for (int h = 0; h < G; h += HW) {
+                if (h < np) {
+                    wave_sync();
+#pragma unroll
+                    for (int p = 0; p < HW; ++p) lvals[lane * SH + p] = o[h + p];
+                    wave_sync();
+                    const int p = lane & 31;
+                    const uint32_t r =
+                        select_halved<SH>(lvals + min(p, HW - 1), n0, keff - (int)bl.z, lane >> 5);
+                    put(a, h + p, lane < HW && h + p < np, r);
+                }
+            }
+            wave_sync();
+        } else {
+            PROBE_ADD(8, 1);
+            PROBE_ADD(9, n0);
+            PROBE_ADD(10, 1);
+            PROBE_MARK(t6);
+            const int nr = (n0 + 63) / 64, nrr = nr <= 2 ? 2 : (nr <= KR / 2 ? KR / 2 : KR), stride = 64 * nrr;
+            uint32_t *vals = (uint32_t *)(scr + X.vals) + (size_t)wv * d.cap * G;
+            for (int e = lane; e < stride; e += 64) {
+                uint32_t o[G];
+                if (e - lane < n0)
+                    item_values<G>(list[(size_t)a * d.items + min(e, n0 - 1)], a, w, d, need2, pool, o);
+#pragma unroll
+                for (int p = 0; p < G; ++p) vals[p * stride + e] = e < n0 ? o[p] : kNone;
+            }
+            // the wave's own stores, read by its other lanes
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t lo = (uint32_t)uni((int)bl.x), hi = (uint32_t)uni((int)bl.y);
+            const int kk = keff - uni((int)bl.z);
+            uint32_t v = lo, res;
+            if (nrr == 2) res = select_windows<2>(vals, np, n0, kk, v, lo, hi, lane);
+            else if (nrr == KR / 2) res = select_windows<KR / 2>(vals, np, n0, kk, v, lo, hi, lane);
+            else res = select_windows<KR>(vals, np, n0, kk, v, lo, hi, lane);
+            put(a, lane, lane < np, res);
+            // the values are read before the next block's are written
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            PROBE_SPAN(11, t6);
+        }
+    }
+    PROBE_SPAN(5, t4);
+}
+
+// The jobs of one group width; NT and LDS are sized for the widest of the launch.
+template <int G, int KR, int WPE>
+__global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE))) k_stream(StreamArgs A) {
+    extern __shared__ __align__(16) float sm[];
+    __shared__ uint32_t next_run;
+    const int NT = blockDim.x, SBW = A.SBW;
+    const int64_t total = A.B.tile_end[A.B.njobs - 1];
+    int64_t gt = blockIdx.x;
+    if (A.B.counter) {
+        if (threadIdx.x == 0) next_run = atomicAdd(A.B.counter, 1u);
+        __syncthreads();
+        gt = next_run;
+    }
+    while (gt < total) {
+        int jb = 0;
+        while (jb + 1 < A.B.njobs && gt >= A.B.tile_end[jb]) ++jb;
+        const ProfileJob &J = A.B.J[jb];
+        const int64_t at = gt - (jb > 0 ? A.B.tile_end[jb - 1] : 0);
+        const int w = J.w;
+        const int ns = (int)((J.Nm + SBW - 1) / SBW);       // strips of a query
+        const int nrun = (ns + A.run - 1) / A.run;
+        const int first = (int)(at % nrun) * A.run, end = min(first + A.run, ns);
+        uint32_t *carry = (uint32_t *)(sm + Lds(G, w, Dims(G, w, NT, SBW)).carry);
+        Strip S;
+        S.J = &J;
+        S.s = (int)(at / nrun);
+        S.in = nullptr;
+        float tmax = 0.0f;
+        // the strip past the run's end, where the run ends inside a tile
+        int i = end < ns && end % A.tile != 0 ? end : end - 1;
+        for (; i >= first; --i) {
+            S.C0 = (int64_t)i * SBW;
+            S.JSe = i < end ? (int)min<int64_t>(SBW, J.Nm - S.C0) : 0;
+            S.CS = S.JSe + w - 1;
+            S.out = carry + (i & 1) * w;
+            __syncthreads();  // the previous strip is done with LDS and the scratch
+            run_strip<G, KR>(S, sm, J.rw + (size_t)blockIdx.x * A.B.slot_floats, NT, SBW, tmax);
+            S.in = i % A.tile != 0 ? S.out : nullptr;
+        }
+        if (J.dmax_bits) {  // max of D (the denominator of eq. 18): one atomic per wave
+            float mx = tmax;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+            if ((threadIdx.x & 63) == 0) atomicMax(J.dmax_bits, __float_as_uint(mx));
+        }
+        if (A.B.counter) {
+            __syncthreads();
+            if (threadIdx.x == 0) next_run = atomicAdd(A.B.counter, 1u);
+            __syncthreads();
+            gt = next_run;
+        } else {
+            gt += gridDim.x;
+        }
+    }
+}
+
+// Kinds of kernel: columns per group, keys per lane (2w + G - 1 <= 64 KR),
+// waves per SIMD.
+constexpr int kKindG[kStreamKinds] = {12, 24, 48, 48};
+constexpr int kKindR[kStreamKinds] = {3, 6, 9, 18};
+constexpr int kKindW[kStreamKinds] = {3, 3, 4, 2};
+const void *const kKernels[kStreamKinds] = {
+    (const void *)k_stream<kKindG[0], kKindR[0], kKindW[0]>, (const void *)k_stream<kKindG[1], kKindR[1], kKindW[1]>,
+    (const void *)k_stream<kKindG[2], kKindR[2], kKindW[2]>, (const void *)k_stream<kKindG[3], kKindR[3], kKindW[3]>};
+int stream_kind(int w) {
+    for (int k = 0; k < kStreamKinds; ++k)
+        if (kKindG[k] == stream_group(w) && 2 * w + kKindG[k] - 1 <= 64 * kKindR[k]) return k;
+    return -1;
+}
+
+constexpr int64_t kRunsPerSlot = 6;
+constexpr size_t kLdsCU = 160 * 1024;
+constexpr size_t kLdsStatic = 512;   // next_run, the vote of __syncthreads_or, alignment
+
+int stream_threads(int w, int SBW) {
+    const int by_col = (SBW + w - 1 + V - 1) / V;
+    const int by_diag = (SBW + 2 * w - 2 + VA - 1 + VA - 1) / VA;
+    return 64 * ((std::max(by_col, by_diag) + 63) / 64);
+}
+
+}  // namespace
+
+size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW) {
+    const int G = stream_group(w);
+    return 4 * (size_t)Lds(G, w, Dims(G, w, stream_threads(wmax, SBW), SBW)).total;
+}
+
+// Where k_profile is the better one (ms, 50 000 points, l = m/2, k_profile
+// against this kernel, regime series / random walk): short windows, w = 33:
+// 6.4 / 5.7 against 7.6 / 7.8, w = 41: 5.7 / 5.3 against 5.9 / 6.1 (w = 49: 5.0
+// / 5.2 against 4.3 / 4.9; below w = 32 k_profile scans each window: w = 26:
+// 16.8 against 9.8); and the first widths of the 1984-window strips, whose
+// groups are coarse for the width, w = 182: 4.5 / 5.6 against 4.3 / 6.2,
+// 200 000 points of a random walk at w = 257: 52 against 61.
+bool stream_takes(int32_t w, int32_t SBW) {
+    if (w < 24 || (w > 31 && w < 48) || (w > 180 && w < 265) || stream_kind(w) < 0) return false;
+    return stream_threads(w, SBW) <= kMaxNT && stream_lds_bytes(w, w, SBW) + kLdsStatic <= kLdsCU;
+}
+
+size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW) {
+    const int G = stream_group(w);
+    return Scratch(G, w, Dims(G, w, stream_threads(wmax, SBW), SBW)).total;
+}
+
+// Workgroups resident at once: LDS and the registers' waves.
+int32_t stream_slots(int32_t w, int32_t SBW) {
+    const int NT = stream_threads(w, SBW);
+    const size_t by_lds = kLdsCU / (stream_lds_bytes(w, w, SBW) + kLdsStatic);
+    const size_t by_waves = 4 * kKindW[stream_kind(w)] / (NT / 64);
+    return 256 * (int32_t)std::max<size_t>(1, std::min(by_lds, by_waves));
+}
+
+hipError_t stream_prepare() {
+    for (const void *k : kKernels) {
+        const hipError_t e =
+            hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsCU - kLdsStatic));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
+                         double share, uint32_t *counter, hipStream_t st) {
+    if (n < 1 || n > kMaxJobs) return hipErrorInvalidValue;
+    int32_t ws[kMaxJobs];
+    for (int i = 0; i < n; ++i) {
+        ws[i] = jobs[i].w;
+        if (!stream_takes(ws[i], SBW)) return hipErrorInvalidValue;
+    }
+    // one launch per group width among the jobs, widest first
+    for (int kind = kStreamKinds - 1; kind >= 0; --kind) {
+        StreamArgs a;
+        a.SBW = SBW;
+        a.B.njobs = 0;
+        a.B.counter = counter ? counter + kind : nullptr;
+        a.B.slot_floats = 0;
+        int32_t wmax = 0;
+        for (int i = 0; i < n; ++i)
+            if (stream_kind(ws[i]) == kind) wmax = std::max(wmax, ws[i]);
+        if (wmax == 0) continue;
+        const int64_t most = std::max<int64_t>(1, (int64_t)(share * stream_slots(wmax, SBW)));
+        // runs as long as leave every workgroup several of them
+        int64_t strips = 0;
+        for (int i = 0; i < n; ++i)
+            if (stream_kind(ws[i]) == kind) strips += ((jobs[i].Nm + SBW - 1) / SBW) * (int64_t)jobs[i].nq;
+        a.tile = tile;
+        a.run = tile;
+        while (a.run > 1 && (a.run % 2 != 0 || strips < kRunsPerSlot * most * a.run)) a.run = a.run % 2 ? 1 : a.run / 2;
+        size_t lds = 0;
+        int64_t acc = 0;
+        for (int i = 0; i < n; ++i) {
+            if (stream_kind(ws[i]) != kind) continue;
+            const int j = a.B.njobs++;
+            a.B.J[j] = jobs[i];
+            const int64_t ns = (jobs[i].Nm + SBW - 1) / SBW;
+            acc += ((ns + a.run - 1) / a.run) * (int64_t)jobs[i].nq;
+            a.B.tile_end[j] = acc;
+            a.B.slot_floats = std::max(a.B.slot_floats, stream_slot_floats(ws[i], wmax, SBW));
+            lds = std::max(lds, stream_lds_bytes(ws[i], wmax, SBW));
+        }
+        const int64_t fit = (int64_t)(scratch_floats / a.B.slot_floats);
+        const int64_t grid = std::min(std::min(acc, fit), most);
+        if (grid < 1 || lds + kLdsStatic > kLdsCU) return hipErrorInvalidValue;
+        void *args[] = {&a};
+        const hipError_t e = hipLaunchKernel(kKernels[kind], dim3((unsigned)grid), dim3(stream_threads(wmax, SBW)),
+                                             args, lds, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace pst
+
+#ifdef PST_PROBE
+// Sums since the last reset: wave cycles of 0 setup and anchors, 1 the first
+// pass, 2 bounds, 3 bounds and their barrier, 4 the second pass, 5 selection,
+// 6 the listed rows' minima in it, 11 counted selections in it; 7 threshold
+// counts, 8 blocks, 9 listed items, 10 counted selections, 12 their steps.
+extern "C" int pst_stream_probe_read(unsigned long long *out, int reset) {
+    static unsigned long long buf[16 * 64];
+    if (hipMemcpyFromSymbol(buf, HIP_SYMBOL(g_stream_probe), sizeof(buf)) != hipSuccess) return -3;
+    for (int i = 0; i < 16; ++i) {
+        out[i] = 0;
+        for (int j = 0; j < 64; ++j) out[i] += buf[i * 64 + j];
+    }
+    if (reset) {
+        static const unsigned long long zero[16 * 64] = {};
+        if (hipMemcpyToSymbol(HIP_SYMBOL(g_stream_probe), zero, sizeof(zero)) != hipSuccess) return -3;
+    }
+    return 0;
+}
+#endif

@@ -1,0 +1,101 @@
+"""The streaming profile kernel against the tiled one, bit for bit: both build
+a cell from the same anchors by the same recurrence and select exactly, so
+their profiles are the same bits.  The tiled kernel is reached through the
+re-anchor period of 2^20 rows, which anchors nowhere.  Sizes at the edges of
+the kernel's kinds (columns per group, keys per lane), of its strips (one
+window, one short, one past) and of its lists (ties, constant stretches,
+extreme order statistics, where every row of a block is listed)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_13680_amd import _lib, api, synth
+
+pytestmark = pytest.mark.gpu
+
+STRIP = {False: 992, True: 1984}   # windows of a strip, w <= 180 or wider
+
+
+def both(call):
+    ctx = api.context(0)
+    ctx.check(ctx.L.pst_set_option(ctx.h, _lib.PST_OPT_ANCHOR_EVERY, 1 << 20))
+    try:
+        ref = call(ctx)
+    finally:
+        ctx.check(ctx.L.pst_set_option(ctx.h, _lib.PST_OPT_ANCHOR_EVERY, 0))
+    return ref, call(ctx)
+
+
+def same_set(x, m, l, k=0):
+    T = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float64)).cuda()
+    (Dr, mr), (D, mx) = both(lambda c: api.profile_set(T, m, l, k, ctx=c))
+    assert torch.equal(D, Dr), (m, l, k, int((D != Dr).sum()), (D != Dr).nonzero()[:3].tolist())
+    assert torch.equal(mx, mr)
+
+
+def series(n, seed):
+    return synth.regime_series(n, seed, synth.SHAPES6, len_range=(400, 2500)).x
+
+
+@pytest.mark.parametrize("w", [24, 31, 48, 58, 59, 79, 80, 116, 117, 148, 149, 180, 181, 264, 265, 392, 393, 513, 552])
+@pytest.mark.parametrize("l", [7, 150])
+def test_widths(w, l):
+    m = w + l - 1
+    same_set(series(4 * m + 2500, w), m, l)
+
+
+@pytest.mark.parametrize("w", [48, 129, 257])
+@pytest.mark.parametrize("extra", [-1, 0, 1, 13])
+@pytest.mark.parametrize("strips", [1, 2, 9])
+def test_ragged_strips(w, extra, strips):
+    l = w - 1 if w < 200 else 64
+    m = w + l - 1
+    windows = strips * STRIP[w > 180] + extra
+    x = series(windows + m - 1, 11)
+    T = torch.from_numpy(x).cuda()
+    Q = torch.from_numpy(series(m, 12)).cuda()
+    ref, got = both(lambda c: api.mpdist_profile(T, Q, l, ctx=c))
+    assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("m,l", [(64, 40), (128, 64), (256, 128), (400, 150), (900, 400)])
+@pytest.mark.parametrize("k", ["1", "2", "w", "2w", "3w"])
+def test_order_statistics(m, l, k):
+    w = m - l + 1
+    same_set(series(3 * m + 2100, 21), m, l, {"1": 1, "2": 2, "w": w, "2w": 2 * w, "3w": 3 * w}[k])
+
+
+@pytest.mark.parametrize("m,l", [(90, 40), (200, 100), (256, 128), (500, 250), (700, 300)])
+@pytest.mark.parametrize("kind", ["steps", "constant", "periodic", "noise", "walk"])
+def test_ties_constants_and_noise(m, l, kind):
+    n = 3 * m + 2300
+    rng = np.random.default_rng(m)
+    if kind == "steps":
+        x = np.repeat(rng.integers(0, 3, n // 7 + 1), 7)[:n].astype(np.float64)
+    elif kind == "constant":  # constant rows and columns among others
+        x = series(n, 31)
+        x[m // 2:2 * m] = 1.5
+        x[n - m - 300:] = -2.0
+    elif kind == "periodic":  # every motif repeats exactly
+        x = np.tile(rng.normal(size=40), n // 40 + 1)[:n]
+    elif kind == "noise":
+        x = rng.normal(size=n)
+    else:
+        x = 40.0 * np.cumsum(rng.normal(size=n))
+    same_set(x, m, l)
+
+
+def test_batch_of_both_kernels_equals_each_alone():
+    """A sweep and a multivariate search whose lengths need several kinds of
+    kernel and the tiled one in one batch."""
+    x = series(7000, 41)
+    T = torch.from_numpy(x).cuda()
+    ms = [50, 64, 70, 128, 200, 330, 420, 600]
+    ref, got = both(lambda c: api.select_length(T, ms, 3, ctx=c))
+    assert ref == got
+    one = api.select_length(T, ms, 3, one_launch=True, graph=False)
+    ref1, got1 = both(lambda c: api.select_length(T, ms, 3, one_launch=True, graph=False, ctx=c))
+    assert ref1 == got1 == one
+    X = torch.from_numpy(np.stack([series(5000, 42 + j) for j in range(3)])).cuda()
+    a, b = both(lambda c: api.snippets_multi(X, 256, 128, 3, ctx=c))
+    assert a == b
