@@ -70,15 +70,21 @@ constexpr int VA = 7;                // diagonals per thread while anchoring
 constexpr int WCOL = 64 * V;         // columns of a wave
 constexpr int RCH = 6;               // rows per step of a pass
 constexpr int kMaxNT = 448;          // threads of the widest strip
-constexpr int KEYR = 18;             // keys per lane, at most: 2w + G - 1 <= 64 * KEYR
 constexpr int kSelect = 64 * 25;     // listed values that a wave holds in LDS
 constexpr int kSelectPad = 32 * 49;  // read past them, never used
 constexpr uint32_t kOne = 0x3F800000u;   // key of y = 1, the largest
 constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
 
-// Columns per group: about w/5, so that a block's bounds stay tight while the
-// group minima of a strip fit LDS.
-__host__ __device__ inline int stream_group(int w) { return w < 80 ? 12 : (w <= 180 ? 24 : 48); }
+// Columns per group: small against w, so that a block's bounds stay tight,
+// while the group minima of a strip leave LDS for the next workgroup.  For w =
+// 181 .. 264 (strips of 1984 windows, two workgroups a CU) they are kept as
+// their upper 16 bits, rounded down: 24 columns in the space of 48 (w = 257,
+// 100 000 points, l = 256: 11.2 -> 9.3 ms; 200 000 points of a walk: 61 -> 46).
+// Wider strips fill a CU's LDS either way; there whole keys of 48 columns are
+// faster (w = 513: 10.7 against 12.0 ms, half the blocks to bound).
+__host__ __device__ inline int stream_group(int w) { return w < 80 ? 12 : (w <= 264 ? 24 : 48); }
+__host__ __device__ inline bool stream_half(int w) { return w > 180 && w <= 264; }
+constexpr int kHalfShift = 14;       // keys are at most kOne = 0x3F800000
 
 struct StreamArgs {
     ProfileBatch B;     // tile_end counts runs
@@ -91,48 +97,51 @@ static_assert(sizeof(StreamArgs) <= 4000, "kernel arguments must fit the 4 KB li
 // Sizes of a strip of w rows in a workgroup of NT threads.
 struct Dims {
     int NW, NC, NG, NGW, ldg, nblk, items, cap;
-    __host__ __device__ Dims(int G, int w, int NT, int SBW) {
+    __host__ __device__ Dims(int G, bool half, int w, int NT, int SBW) {
         NW = NT / 64;
         NC = NT * V;                       // columns of the workgroup's threads
         NG = (SBW + w - 1 + G - 1) / G;    // groups with columns of the strip
-        NGW = (NG + 31) / 32;              // mask words per row
-        ldg = (NG + 1) | 1;                // row stride of the group minima, one past the end (odd: lanes = rows)
+        NGW = (NG + 15) / 16;              // words of a row's groups to keep
+        // row stride of the group minima, one past the end; odd in words (lanes = rows)
+        ldg = half ? 2 * (((NG + 2) / 2) | 1) : (NG + 1) | 1;
         nblk = (SBW + G - 1) / G;          // blocks of G windows
         items = 2 * w + G - 1;             // rows and columns of a block's windows
-        cap = 64 * (G == 48 ? KEYR : G / 4);   // listed values a wave holds in scratch
+        cap = 64 * (half ? 9 : (G == 48 ? 18 : G / 4));   // listed values a wave holds in scratch
     }
 };
 
 // LDS of a strip, in floats.
 struct Lds {
     int rst, bnd, col, carry, need, blk, bm, total, wp;
-    __host__ __device__ Lds(int G, int w, const Dims &d) {
+    __host__ __device__ Lds(bool half, int w, const Dims &d) {
         wp = (w + RCH + 3) & ~3;
         rst = 0;                                 // float4 [w]: {inv/2, df, dg, h/2}
         bnd = rst + 4 * w;                       // [NW][wp] covariance left of each wave's columns
         col = bnd + d.NW * wp;                   // [NC] anchors of row 0, then column minima
         carry = col + d.NC;                      // [2][w] column minima of the strip to the right
-        need = (carry + 2 * w + 1) & ~1;         // uint2 [w][NGW]: groups to keep, slots before
-        blk = need + 2 * w * d.NGW;              // [nblk] {lo, hi, below, listed}
+        need = carry + 2 * w;                    // [w][NGW] 16 groups to keep, slots before them << 16
+        blk = need + w * d.NGW;                  // [nblk] {lo, hi, below, listed}
         blk = (blk + 3) & ~3;
         bm = blk + 4 * d.nblk;                   // [w][ldg] group minima; the anchors' staging before
         const int lists = d.NW * kSelect + kSelectPad;   // later each wave's listed values
-        const int mins = (w * d.ldg + 3) & ~3;
+        const int mins = ((half ? w * d.ldg / 2 : w * d.ldg) + 3) & ~3;
         total = bm + (mins > lists ? mins : lists);
     }
 };
 
 // Scratch of one workgroup, in floats: the kept pieces of y, the lists, the
-// listed values of each wave.
+// listed values of each wave, exact group minima.
 struct Scratch {
-    size_t pool, list, vals, total;
-    __host__ __device__ Scratch(int G, int w, const Dims &d) {
+    size_t pool, list, vals, mins, total;
+    __host__ __device__ Scratch(int G, bool half, int w, const Dims &d) {
         pool = 64;                                          // reads may start a value early
         list = pool + (size_t)w * d.NG * G + 4 * G;             // and run past the last piece
         list = (list + 63) & ~(size_t)63;
         vals = list + 2 * (size_t)d.nblk * d.items;
         vals = (vals + 63) & ~(size_t)63;
-        total = vals + (size_t)d.NW * d.cap * G;
+        mins = vals + (size_t)d.NW * d.cap * G;
+        mins = (mins + 63) & ~(size_t)63;
+        total = mins + (half ? (size_t)w * d.NG + 4 : 0);   // exact group minima [w][NG]
         total = (total + 63) & ~(size_t)63;
     }
 };
@@ -291,10 +300,18 @@ __device__ __forceinline__ uint32_t group_min(const uint32_t (&y)[V]) {
 
 // First pass: column minima into colmin, group minima into bm, the covariance
 // left of each wave into bnd.  Wave k runs a step behind wave k-1.
-template <int G, bool CONST>
+template <int G, bool H, bool CONST>
 __device__ __forceinline__ void pass_one(const Cols &c, uint32_t (&colmin)[V], const float4 *rst, float *bnd, int wp,
-                                         uint32_t *bm, int ldg, int NG, int w, int nwa, int wv,
+                                         uint32_t *bm, uint32_t *gm, int ldg, int NG, int w, int nwa, int wv,
                                          int lane) {
+    auto keep = [&](int i, int g, uint32_t m) {
+        if constexpr (H) {
+            ((uint16_t *)bm)[i * ldg + g] = (uint16_t)(m >> kHalfShift);
+            gm[i * NG + g] = m;
+        } else {
+            bm[i * ldg + g] = m;
+        }
+    };
     const int nch = (w + RCH - 1) / RCH;
     const int g = (wv * 64 + lane) / (G / V);
     const bool lead = lane % (G / V) == 0 && g < NG;
@@ -331,7 +348,7 @@ __device__ __forceinline__ void pass_one(const Cols &c, uint32_t (&colmin)[V], c
                 }
                 if (lead) {
 #pragma unroll
-                    for (int e = 0; e < RCH; ++e) bm[(r0 + e) * ldg + g] = mg[e];
+                    for (int e = 0; e < RCH; ++e) keep(r0 + e, g, mg[e]);
                 }
                 if (lane == 63 && wv + 1 < nwa) {
 #pragma unroll
@@ -345,7 +362,7 @@ __device__ __forceinline__ void pass_one(const Cols &c, uint32_t (&colmin)[V], c
 #pragma unroll
                     for (int v = 0; v < V; ++v) colmin[v] = min(colmin[v], y[v]);
                     const uint32_t m = group_min<G>(y);
-                    if (lead) bm[i * ldg + g] = m;
+                    if (lead) keep(i, g, m);
                     if (lane == 63 && wv + 1 < nwa) rb[i + 1] = out;
                 }
             }
@@ -354,21 +371,21 @@ __device__ __forceinline__ void pass_one(const Cols &c, uint32_t (&colmin)[V], c
     }
 }
 
-// Second pass: the pieces of y named in need (this wave's mask word of each
-// row and the slots before it) into the pool.
+// Second pass: the pieces of y named in need (16 groups of a row to a word,
+// the slots before them in its upper half) into the pool.
 template <int G, bool CONST>
-__device__ __forceinline__ void pass_two(const Cols &c, const float4 *rst, const float *lb, const uint2 *need, int ngw,
-                                         int NG, float *pool, int w, int t) {
+__device__ __forceinline__ void pass_two(const Cols &c, const float4 *rst, const float *lb, const uint32_t *need,
+                                         int ngw, int NG, float *pool, int w, int t) {
     const int g = t / (G / V);
-    const uint32_t bit = g < NG ? 1u << (g & 31) : 0u;
-    const uint2 *nd = need + uni(min(g >> 5, ngw - 1));
+    const uint32_t bit = g < NG ? 1u << (g & 15) : 0u;
+    const uint32_t *nd = need + min(g >> 4, ngw - 1);
     float *mine = pool + (t % (G / V)) * V;
     float cov[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) cov[v] = c.cov0[v];
-    auto keep = [&](const uint32_t (&y)[V], const uint2 &q) {
-        if (q.x & bit) {
-            float2 *p = (float2 *)(mine + (size_t)(q.y + __popc(q.x & (bit - 1u))) * G);
+    auto keep = [&](const uint32_t (&y)[V], uint32_t q) {
+        if (q & bit) {
+            float2 *p = (float2 *)(mine + (size_t)((q >> 16) + __popc(q & (bit - 1u))) * G);
             p[0] = make_float2(__uint_as_float(y[0]), __uint_as_float(y[1]));
             p[1] = make_float2(__uint_as_float(y[2]), __uint_as_float(y[3]));
             p[2] = make_float2(__uint_as_float(y[4]), __uint_as_float(y[5]));
@@ -378,7 +395,7 @@ __device__ __forceinline__ void pass_two(const Cols &c, const float4 *rst, const
     for (; i + RCH <= w; i += RCH) {
         float4 rr[RCH];
         float lf[RCH];
-        uint2 q[RCH];
+        uint32_t q[RCH];
 #pragma unroll
         for (int e = 0; e < RCH; ++e) {
             rr[e] = rst[i + e];
@@ -459,8 +476,8 @@ __device__ __forceinline__ uint32_t find_rank(const uint32_t (&K)[NR], int k, in
 // The same from a guess x and the spacing of the keys around it: steps that
 // double until rank k is bracketed.
 template <int NR>
-__device__ __forceinline__ uint32_t find_from(const uint32_t (&K)[NR], int k, int x, int step, int xl, int cl, int top,
-                                              int slack) {
+__device__ __forceinline__ uint32_t find_from(const uint32_t (&K)[NR], int k, int x, int step, int most, int xl,
+                                              int cl, int top, int slack) {
     int xh = top, ch = 64 * NR;
     x = min(max(x, xl + 1), xh - 1);
     while (x > xl && x < xh) {
@@ -476,20 +493,21 @@ __device__ __forceinline__ uint32_t find_from(const uint32_t (&K)[NR], int k, in
             xl = x;
             cl = c;
             if (cl == k - 1 || ch != 64 * NR) break;
-            x += min(step * (k - c), (int)kOne);
+            x += min(step * (k - c), top);
         }
-        step = min(step * 2, 1 << 20);
+        step = min(step * 2, most);
     }
     if (ch == 64 * NR) ch = count_le<NR>(K, (uint32_t)xh);
     if (ch < k) return (uint32_t)top;    // fewer than k keys: the largest y there is
     return find_rank<NR>(K, k, xl, cl, xh, ch, slack);
 }
 
-// U and C of this lane's rows for block a: the groups a .. a + GC + GE hold the
-// columns of the block's windows, a+1 .. a+GC lie inside every one of them.
-template <int NR, int GC, int GE>
-__device__ __forceinline__ void row_keys(uint32_t (&U)[NR], uint32_t (&C)[NR], const uint32_t *bm, int ldg, int w, int a,
-                                         int lane) {
+// U and C of this lane's rows for block a: the groups a .. a + gc + ge hold the
+// columns of the block's windows, a+1 .. a+gc lie inside every one of them.
+// GC > 0: gc, GE: ge (fixed loads); GC = 0: any gc >= 4.
+template <typename T, int NR, int GC, int GE>
+__device__ __forceinline__ void row_keys(uint32_t (&U)[NR], uint32_t (&C)[NR], const T *bm, int ldg, int w, int a,
+                                         int lane, int gc, int ge) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         U[r] = kNone;
@@ -497,71 +515,88 @@ __device__ __forceinline__ void row_keys(uint32_t (&U)[NR], uint32_t (&C)[NR], c
         if (64 * r < w) {
             const int x = lane + 64 * r;
             if (x < w) {
-                const uint32_t *row = bm + x * ldg + a;
-                uint32_t m[GC + GE + 1];
+                const T *row = bm + x * ldg + a;
+                uint32_t c = kNone, u;
+                if constexpr (GC > 0) {
+                    uint32_t m[GC + GE + 1];
 #pragma unroll
-                for (int q = 0; q <= GC + GE; ++q) m[q] = row[q];
-                uint32_t c = m[1];
+                    for (int q = 0; q <= GC + GE; ++q) m[q] = row[q];
 #pragma unroll
-                for (int q = 2; q <= GC; ++q) c = min(c, m[q]);
-                uint32_t u = min(c, m[0]);
+                    for (int q = 1; q <= GC; ++q) c = min(c, m[q]);
+                    u = min(c, m[0]);
 #pragma unroll
-                for (int q = GC + 1; q <= GC + GE; ++q) u = min(u, m[q]);
+                    for (int q = GC + 1; q <= GC + GE; ++q) u = min(u, m[q]);
+                } else {
+                    const uint32_t m0 = row[0], e1 = row[gc + 1], e2 = row[gc + ge];
+                    for (int q = 0; q < gc; q += 4) {   // the last four overlap the ones before
+                        const T *p = row + 1 + min(q, gc - 4);
+                        const uint32_t m1 = p[0], m2 = p[1], m3 = p[2], m4 = p[3];
+                        c = min(min(min(c, m1), m2), min(m3, m4));
+                    }
+                    u = min(min(min(c, m0), e1), e2);
+                }
                 U[r] = u;
                 C[r] = c;
             }
         }
     }
 }
-template <int NR, int GC0, int GC1>
-__device__ __forceinline__ void row_keys_of(uint32_t (&U)[NR], uint32_t (&C)[NR], const uint32_t *bm, int ldg, int w,
-                                            int a, int lane, int gc, int ge) {
+template <typename T, int NR, int GC0, int GC1>
+__device__ __forceinline__ void row_keys_of(uint32_t (&U)[NR], uint32_t (&C)[NR], const T *bm, int ldg, int w, int a,
+                                            int lane, int gc, int ge) {
     if constexpr (GC0 < GC1) {
         if (gc > GC0) {
-            row_keys_of<NR, GC0 + 1, GC1>(U, C, bm, ldg, w, a, lane, gc, ge);
+            row_keys_of<T, NR, GC0 + 1, GC1>(U, C, bm, ldg, w, a, lane, gc, ge);
             return;
         }
     }
-    if (ge <= 1) row_keys<NR, GC0, 1>(U, C, bm, ldg, w, a, lane);
-    else row_keys<NR, GC0, 2>(U, C, bm, ldg, w, a, lane);
+    if (ge <= 1) row_keys<T, NR, GC0, 1>(U, C, bm, ldg, w, a, lane, gc, ge);
+    else row_keys<T, NR, GC0, 2>(U, C, bm, ldg, w, a, lane, gc, ge);
 }
 
 // Bounds and lists of the blocks [a0, a1) of a strip, by one wave; lane + 64 r
 // is row i < w or column x - w of the block's columns.  GC0 .. GC1: the whole
-// groups inside a block's windows.
-template <int G, int NR, int GC0, int GC1>
+// groups inside a block's windows (0: any).  H: the keys are the upper halves,
+// rounded down, of the group minima and of the columns alike; a bound lo or hi
+// then stands for all keys with that upper half.
+template <int G, bool H, int NR, int GC0, int GC1>
 __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int CS, const Dims &d, const uint32_t *bm,
                                              const uint32_t *colk, uint32_t *need, uint4 *blk, uint2 *list, int lane) {
+    constexpr int SH = H ? kHalfShift : 0;
+    constexpr int kTop = (int)(kOne >> SH), kStep0 = H ? 1 : 1 << 10, kStep1 = H ? 64 : 1 << 20;
     const int gc = w / G - 1;                 // groups a+1 .. a+gc lie inside every window of the block
     const int ge = 1 + (w - 2) / G - gc;      // groups past them that hold a column of its windows
     const int rem = w % G;
     uint32_t U[NR], C[NR];
-    uint32_t lo = 0x3D800000u, hi = lo;       // guesses: y = 1/16, then the block before
+    uint32_t lo = 0x3D800000u >> SH, hi = lo; // guesses: y = 1/16, then the block before
     for (int a = a0; a < a1; ++a) {
-        row_keys_of<NR, GC0, GC1>(U, C, bm, d.ldg, w, a, lane, gc, ge);
+        if constexpr (H) row_keys<uint16_t, NR, 0, 0>(U, C, (const uint16_t *)bm, d.ldg, w, a, lane, gc, ge);
+        else row_keys_of<uint32_t, NR, GC0, GC1>(U, C, bm, d.ldg, w, a, lane, gc, ge);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             if (64 * r + 63 >= w) {
                 const int cx = lane + 64 * r - w, cg = a * G + cx;
                 if (cx >= 0 && cx < w + G - 1 && cg < CS) {
-                    const uint32_t u = colk[cg];
+                    const uint32_t u = colk[cg] >> SH;
                     U[r] = u;
                     C[r] = cx >= G - 1 && cx < w ? u : kNone;
                 }
             }
         }
     // lo: the k-th smallest U; hi: no less than the k-th smallest C
-        const int span = max((int)(hi - lo), 1 << 10);
-        lo = find_from<NR>(U, k, (int)lo, min(max(span / 8, 1 << 10), 1 << 20), -1, 0, (int)kOne, -1);
+        const int span = max((int)(hi - lo), kStep0), step = min(max(span / 8, kStep0), kStep1);
+        lo = find_from<NR>(U, k, (int)lo, step, kStep1, -1, 0, kTop, -1);
         const int ce = count_le<NR>(C, lo);
-        if (ce >= k) {
-            if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
+        if (ce >= k || lo >= (uint32_t)kTop) {
             hi = lo;
+        } else {
+            hi = find_from<NR>(C, k, (int)max(hi, lo + (uint32_t)span / 2), step, kStep1, (int)lo, ce, kTop,
+                               2 + (k >> 4));
+        }
+        if (!H && ce >= k) {
+            if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
             continue;
         }
-        hi = lo >= kOne ? kOne
-                        : find_from<NR>(C, k, (int)max(hi, lo + (uint32_t)span / 2), min(max(span / 8, 1 << 10), 1 << 20), (int)lo, ce,
-                                        (int)kOne, 2 + (k >> 4));
         // below lo everywhere; listed: the rest that may be at most hi
         int below = 0, n = 0;
         uint2 *la = list + (size_t)a * d.items;
@@ -578,36 +613,39 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
                 const int pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                               __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
                 const bool isrow = x < w;
-                la[pos] = make_uint2(isrow ? (uint32_t)x : 0x80000000u | (uint32_t)(x - w), isrow ? C[r] : U[r]);
+                la[pos] = isrow ? make_uint2((uint32_t)x, C[r])
+                                : make_uint2(0x80000000u | (uint32_t)(x - w), colk[a * G + x - w]);
                 if (64 * r < w && isrow) {
-                    uint32_t *nd = need + 2 * (x * d.NGW);
-                    atomicOr(nd + 2 * (a >> 5), 1u << (a & 31));
-                    if (gr < d.NG) atomicOr(nd + 2 * (gr >> 5), 1u << (gr & 31));
-                    if (rem >= 2 && gr + 1 < d.NG) atomicOr(nd + 2 * ((gr + 1) >> 5), 1u << ((gr + 1) & 31));
+                    uint32_t *nd = need + x * d.NGW;
+                    atomicOr(nd + (a >> 4), 1u << (a & 15));
+                    if (gr < d.NG) atomicOr(nd + (gr >> 4), 1u << (gr & 15));
+                    if (rem >= 2 && gr + 1 < d.NG) atomicOr(nd + ((gr + 1) >> 4), 1u << ((gr + 1) & 15));
                 }
             }
             n += __popcll(m);
         }
-        if (lane == 0) blk[a] = make_uint4(lo, hi, (uint32_t)below, (uint32_t)n);
+        if (lane == 0)
+            blk[a] = make_uint4(lo << SH, (hi << SH) | ((1u << SH) - 1u), (uint32_t)below, (uint32_t)n);
     }
 }
 
 // block_bounds with the registers that w needs.
-template <int G, int KR>
+template <int G, bool H, int KR>
 __device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int CS, const Dims &d, const uint32_t *bm,
                                              const uint32_t *colk, uint32_t *need, uint4 *blk, uint2 *list, int lane) {
     const int nr = (d.items + 63) / 64;
-#define BOUNDS(NR, GC0, GC1) block_bounds<G, NR, GC0, GC1>(a0, a1, w, k, CS, d, bm, colk, need, blk, list, lane)
+#define BOUNDS(NR, GC0, GC1) block_bounds<G, H, NR, GC0, GC1>(a0, a1, w, k, CS, d, bm, colk, need, blk, list, lane)
     // the widths of each kind: see stream_group and kKindR
     if constexpr (G == 12) {
         if (nr <= 2) BOUNDS(2, 1, 4);
         else BOUNDS(3, 3, 5);
-    } else if constexpr (G == 24) {
+    } else if constexpr (G == 24 && !H) {
         if (nr <= 4) BOUNDS(4, 2, 3);
         else if (nr == 5) BOUNDS(5, 3, 5);
         else BOUNDS(6, 4, 6);
-    } else if constexpr (KR <= 9) {
-        BOUNDS(9, 2, 4);
+    } else if constexpr (H) {
+        if (nr <= 7) BOUNDS(7, 0, 0);
+        else BOUNDS(9, 0, 0);
     } else {
         if (nr <= 13) BOUNDS(13, 4, 7);
         else BOUNDS(18, 6, 10);
@@ -616,9 +654,9 @@ __device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int C
 }
 
 // One listed item of block a over the block's G windows, by one lane.
-template <int G>
-__device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &d, const uint2 *need,
-                                            const float *pool, uint32_t (&o)[G]) {
+template <int G, bool H>
+__device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &d, const uint32_t *need,
+                                            const float *pool, const uint32_t *gm, uint32_t (&o)[G]) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef f4 f4u __attribute__((aligned(4)));
     if (it.x & 0x80000000u) {  // a column: in the windows that hold it
@@ -626,12 +664,12 @@ __device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &
 #pragma unroll
         for (int p = 0; p < G; ++p) o[p] = (p <= cx && p >= cx - w + 1) ? it.y : kNone;
     } else {
-        // a row: suffix minima of its group, the whole groups inside (it.y),
-        // and running minima of the columns that follow
-        const uint2 *nd = need + (int)it.x * d.NGW;
+        // a row: suffix minima of its group, the whole groups inside (it.y, or
+        // their exact minima gm), and running minima of the columns that follow
+        const uint32_t *nd = need + (int)it.x * d.NGW;
         auto slot = [&](int g) {
-            const uint2 q = nd[min(g >> 5, d.NGW - 1)];
-            return (int)(q.y + __popc(q.x & ((1u << (g & 31)) - 1u)));
+            const uint32_t q = nd[min(g >> 4, d.NGW - 1)];
+            return (int)((q >> 16) + __popc(q & ((1u << (g & 15)) - 1u)));
         };
         const float *pa = pool + (size_t)slot(a) * G;
         const int rem = w % G;
@@ -644,6 +682,17 @@ __device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &
             for (int e = 0; e < 4; ++e) o[p + e] = bits(q[e]);
         }
         uint32_t run = it.y;
+        if constexpr (H) {
+            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+            typedef u4 u4u __attribute__((aligned(4)));
+            const uint32_t *inner = gm + (int)it.x * d.NG + a + 1;
+            const int gc = w / G - 1;
+            run = kNone;
+            for (int q = 0; q < gc; q += 4) {   // the last four overlap the ones before
+                const u4 m = *(const u4u *)(inner + min(q, gc - 4));
+                run = min(min(min(run, m[0]), m[1]), min(m[2], m[3]));
+            }
+        }
         for (int x = 0; x < rem - 1; x += 4) {  // columns 0 .. rem-2 (those past it repeat nothing)
             const f4 q = *(const f4 *)(pr + x);
             run = min(run, bits(q[0]));
@@ -652,19 +701,14 @@ __device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &
         }
 #pragma unroll
         for (int p = G - 2; p >= 0; --p) o[p] = min(o[p], o[p + 1]);
-        constexpr int H = G < 24 ? G : 24;   // loads in flight
+        f4 t[G / 4];
 #pragma unroll
-        for (int h = 0; h < G; h += H) {
-            f4 t[H / 4];
+        for (int p = 0; p < G / 4; ++p) t[p] = *(const f4u *)(pt + 4 * p);
 #pragma unroll
-            for (int p = 0; p < H / 4; ++p) t[p] = *(const f4u *)(pt + h + 4 * p);
-#pragma unroll
-            for (int p = 0; p < H; ++p) {
-                const uint32_t y = h + p == 0 && rem == 0 ? kNone : bits(t[p / 4][p % 4]);
-                run = min(run, y);
-                o[h + p] = min(o[h + p], run);
-            }
-            if (G > H) __builtin_amdgcn_sched_barrier(0);
+        for (int p = 0; p < G; ++p) {
+            const uint32_t y = p == 0 && rem == 0 ? kNone : bits(t[p / 4][p % 4]);
+            run = min(run, y);
+            o[p] = min(o[p], run);
         }
     }
 }
@@ -757,7 +801,7 @@ struct Strip {
     uint32_t *out;      // minima of the first w-1 columns, for the strip to the left
 };
 
-template <int G, int KR>
+template <int G, bool H, int KR>
 __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr, int NT, int SBW, float &tmax) {
     const ProfileJob &J = *S.J;
     // opaque to the compiler, so that nothing computed from them is kept in
@@ -765,9 +809,9 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     int w = J.w, t = threadIdx.x;
     asm volatile("" : "+s"(w), "+s"(NT), "+s"(SBW), "+v"(t));
     const int l = J.l;
-    const Dims d(G, w, NT, SBW);
-    const Lds L(G, w, d);
-    const Scratch X(G, w, d);
+    const Dims d(G, H, w, NT, SBW);
+    const Lds L(H, w, d);
+    const Scratch X(G, H, w, d);
     const int wv = uni(t >> 6), lane = t & 63;
     const int64_t rb = (int64_t)S.s * J.row_stride;
     float4 *rst = (float4 *)(sm + L.rst);
@@ -776,6 +820,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     uint32_t *need = (uint32_t *)(sm + L.need);
     uint4 *blk = (uint4 *)(sm + L.blk);
     uint32_t *bm = (uint32_t *)(sm + L.bm);
+    uint32_t *gm = (uint32_t *)(scr + X.mins);
     const int CS = S.CS;
     const int nwa = (CS + WCOL - 1) / WCOL;   // waves with columns
 
@@ -788,7 +833,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
         rst[i] = make_float4(0.5f * J.row.inv[r], J.row.df[r], J.row.dg[r], 0.5f * hr);
         crow |= hr != 0.0f;
     }
-    for (int i = t; i < w * d.NGW; i += NT) need[2 * i] = 0u;
+    for (int i = t; i < w * d.NGW; i += NT) need[i] = 0u;
     for (int i = CS + t; i < d.NC; i += NT) col[i] = 0.0f;
     const int ndg = CS + w - 1;
     const int off = (VA - (w - 1) % VA) % VA;
@@ -834,9 +879,9 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     PROBE_SPAN(0, t0);
     PROBE_MARK(t1);
     if (any_const)
-        pass_one<G, true>(c, colmin, rst, bnd, L.wp, bm, d.ldg, d.NG, w, nwa, wv, lane);
+        pass_one<G, H, true>(c, colmin, rst, bnd, L.wp, bm, gm, d.ldg, d.NG, w, nwa, wv, lane);
     else
-        pass_one<G, false>(c, colmin, rst, bnd, L.wp, bm, d.ldg, d.NG, w, nwa, wv, lane);
+        pass_one<G, H, false>(c, colmin, rst, bnd, L.wp, bm, gm, d.ldg, d.NG, w, nwa, wv, lane);
     uint32_t *colk = (uint32_t *)col;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -848,7 +893,10 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     if (S.JSe == 0) return;
     // groups past the last active wave hold nothing
     for (int i = t; i < w; i += NT)
-        for (int g = min(nwa * (WCOL / G), d.NG); g <= d.NG; ++g) bm[i * d.ldg + g] = kOne;
+        for (int g = min(nwa * (WCOL / G), d.NG); g <= d.NG; ++g) {
+            if constexpr (H) ((uint16_t *)bm)[i * d.ldg + g] = (uint16_t)(kOne >> kHalfShift);
+            else bm[i * d.ldg + g] = kOne;
+        }
     lds_barrier();
 
     float *pool = scr + X.pool;
@@ -856,19 +904,18 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     const int nblk = (S.JSe + G - 1) / G;
     const int per = (nblk + d.NW - 1) / d.NW;
     PROBE_MARK(t2);
-    strip_bounds<G, KR>(min(wv * per, nblk), min(wv * per + per, nblk), w, min(J.k, 2 * w), CS, d, bm, colk, need, blk,
+    strip_bounds<G, H, KR>(min(wv * per, nblk), min(wv * per + per, nblk), w, min(J.k, 2 * w), CS, d, bm, colk, need, blk,
                     list, lane);
     PROBE_SPAN(2, t2);
     __syncthreads();
     PROBE_SPAN(3, t2);
     PROBE_MARK(t3);
     // slots of the kept pieces, in (row, group) order
-    const uint2 *need2 = (const uint2 *)need;
     if (wv == 0) {
         const int tot = w * d.NGW, pl = (tot + 63) / 64;
         const int b = lane * pl, e = min(b + pl, tot);
         int sum = 0;
-        for (int i = b; i < e; ++i) sum += __popc(need[2 * i]);
+        for (int i = b; i < e; ++i) sum += __popc(need[i]);
         int inc = sum;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -877,17 +924,18 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
         }
         int at = inc - sum;
         for (int i = b; i < e; ++i) {
-            need[2 * i + 1] = (uint32_t)at;
-            at += __popc(need[2 * i]);
+            const uint32_t q = need[i];
+            need[i] = q | (uint32_t)at << 16;
+            at += __popc(q);
         }
     }
     lds_barrier();
     if (wv < nwa) {
         const float *lb = bnd + wv * L.wp;
         if (any_const)
-            pass_two<G, true>(c, rst, lb, need2, d.NGW, d.NG, pool, w, t);
+            pass_two<G, true>(c, rst, lb, need, d.NGW, d.NG, pool, w, t);
         else
-            pass_two<G, false>(c, rst, lb, need2, d.NGW, d.NG, pool, w, t);
+            pass_two<G, false>(c, rst, lb, need, d.NGW, d.NG, pool, w, t);
     }
     __syncthreads();
     PROBE_SPAN(4, t3);
@@ -927,7 +975,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
             PROBE_ADD(9, T);
             if (lane < T) {
                 uint32_t o[G];
-                item_values<G>(list[(size_t)ita * d.items + (lane - itb)], ita, w, d, need2, pool, o);
+                item_values<G, H>(list[(size_t)ita * d.items + (lane - itb)], ita, w, d, need, pool, gm, o);
 #pragma unroll
                 for (int p = 0; p < G; ++p) lvals[lane * ST + p] = o[p];
             }
@@ -967,17 +1015,17 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
             T += n0;
             nmax = max(nmax, n0);
         } else if (n0 <= 64) {
-            constexpr int HW = G < 24 ? G : 24, SH = HW + 1;
             PROBE_MARK(t5);
             PROBE_ADD(8, 1);
             PROBE_ADD(9, n0);
             uint32_t o[G];
-            item_values<G>(list[(size_t)a * d.items + min(lane, n0 - 1)], a, w, d, need2, pool, o);
+            item_values<G, H>(list[(size_t)a * d.items + min(lane, n0 - 1)], a, w, d, need, pool, gm, o);
             PROBE_SPAN(6, t5);
+            // (the values of gathered blocks, if any, are not in LDS yet)
+            constexpr int HW = G < 24 ? G : 24, SH = HW + 1;
 #pragma unroll
             for (int h = 0; h < G; h += HW) {
                 if (h < np) {
-                    wave_sync();
 #pragma unroll
                     for (int p = 0; p < HW; ++p) lvals[lane * SH + p] = o[h + p];
                     wave_sync();
@@ -985,9 +1033,9 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
                     const uint32_t r =
                         select_halved<SH>(lvals + min(p, HW - 1), n0, keff - (int)bl.z, lane >> 5);
                     put(a, h + p, lane < HW && h + p < np, r);
+                    wave_sync();
                 }
             }
-            wave_sync();
         } else {
             PROBE_ADD(8, 1);
             PROBE_ADD(9, n0);
@@ -998,7 +1046,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
             for (int e = lane; e < stride; e += 64) {
                 uint32_t o[G];
                 if (e - lane < n0)
-                    item_values<G>(list[(size_t)a * d.items + min(e, n0 - 1)], a, w, d, need2, pool, o);
+                    item_values<G, H>(list[(size_t)a * d.items + min(e, n0 - 1)], a, w, d, need, pool, gm, o);
 #pragma unroll
                 for (int p = 0; p < G; ++p) vals[p * stride + e] = e < n0 ? o[p] : kNone;
             }
@@ -1022,7 +1070,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
 }
 
 // The jobs of one group width; NT and LDS are sized for the widest of the launch.
-template <int G, int KR, int WPE>
+template <int G, bool H, int KR, int WPE>
 __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE))) k_stream(StreamArgs A) {
     extern __shared__ __align__(16) float sm[];
     __shared__ uint32_t next_run;
@@ -1043,7 +1091,7 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
         const int ns = (int)((J.Nm + SBW - 1) / SBW);       // strips of a query
         const int nrun = (ns + A.run - 1) / A.run;
         const int first = (int)(at % nrun) * A.run, end = min(first + A.run, ns);
-        uint32_t *carry = (uint32_t *)(sm + Lds(G, w, Dims(G, w, NT, SBW)).carry);
+        uint32_t *carry = (uint32_t *)(sm + Lds(H, w, Dims(G, H, w, NT, SBW)).carry);
         Strip S;
         S.J = &J;
         S.s = (int)(at / nrun);
@@ -1057,7 +1105,7 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
             S.CS = S.JSe + w - 1;
             S.out = carry + (i & 1) * w;
             __syncthreads();  // the previous strip is done with LDS and the scratch
-            run_strip<G, KR>(S, sm, J.rw + (size_t)blockIdx.x * A.B.slot_floats, NT, SBW, tmax);
+            run_strip<G, H, KR>(S, sm, J.rw + (size_t)blockIdx.x * A.B.slot_floats, NT, SBW, tmax);
             S.in = i % A.tile != 0 ? S.out : nullptr;
         }
         if (J.dmax_bits) {  // max of D (the denominator of eq. 18): one atomic per wave
@@ -1077,17 +1125,21 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
     }
 }
 
-// Kinds of kernel: columns per group, keys per lane (2w + G - 1 <= 64 KR),
-// waves per SIMD.
-constexpr int kKindG[kStreamKinds] = {12, 24, 48, 48};
+// Kinds of kernel: columns per group, half keys, keys per lane (2w + G - 1 <=
+// 64 KR), waves per SIMD.
+constexpr int kKindG[kStreamKinds] = {12, 24, 24, 48};
+constexpr bool kKindH[kStreamKinds] = {false, false, true, false};
 constexpr int kKindR[kStreamKinds] = {3, 6, 9, 18};
 constexpr int kKindW[kStreamKinds] = {3, 3, 4, 2};
 const void *const kKernels[kStreamKinds] = {
-    (const void *)k_stream<kKindG[0], kKindR[0], kKindW[0]>, (const void *)k_stream<kKindG[1], kKindR[1], kKindW[1]>,
-    (const void *)k_stream<kKindG[2], kKindR[2], kKindW[2]>, (const void *)k_stream<kKindG[3], kKindR[3], kKindW[3]>};
+    (const void *)k_stream<kKindG[0], kKindH[0], kKindR[0], kKindW[0]>,
+    (const void *)k_stream<kKindG[1], kKindH[1], kKindR[1], kKindW[1]>,
+    (const void *)k_stream<kKindG[2], kKindH[2], kKindR[2], kKindW[2]>,
+    (const void *)k_stream<kKindG[3], kKindH[3], kKindR[3], kKindW[3]>};
 int stream_kind(int w) {
     for (int k = 0; k < kStreamKinds; ++k)
-        if (kKindG[k] == stream_group(w) && 2 * w + kKindG[k] - 1 <= 64 * kKindR[k]) return k;
+        if (kKindG[k] == stream_group(w) && kKindH[k] == stream_half(w) && 2 * w + kKindG[k] - 1 <= 64 * kKindR[k])
+            return k;
     return -1;
 }
 
@@ -1104,25 +1156,24 @@ int stream_threads(int w, int SBW) {
 }  // namespace
 
 size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW) {
-    const int G = stream_group(w);
-    return 4 * (size_t)Lds(G, w, Dims(G, w, stream_threads(wmax, SBW), SBW)).total;
+    const bool H = stream_half(w);
+    return 4 * (size_t)Lds(H, w, Dims(stream_group(w), H, w, stream_threads(wmax, SBW), SBW)).total;
 }
 
 // Where k_profile is the better one (ms, 50 000 points, l = m/2, k_profile
 // against this kernel, regime series / random walk): short windows, w = 33:
-// 6.4 / 5.7 against 7.6 / 7.8, w = 41: 5.7 / 5.3 against 5.9 / 6.1 (w = 49: 5.0
-// / 5.2 against 4.3 / 4.9; below w = 32 k_profile scans each window: w = 26:
-// 16.8 against 9.8); and the first widths of the 1984-window strips, whose
-// groups are coarse for the width, w = 182: 4.5 / 5.6 against 4.3 / 6.2,
-// 200 000 points of a random walk at w = 257: 52 against 61.
+// 6.4 / 5.7 against 7.6 / 7.8, w = 41: 5.7 / 5.3 against 5.9 / 6.1; w = 49: 5.0
+// / 5.2 against 4.3 / 4.9.  Below w = 32 k_profile scans each window: w = 26:
+// 16.8 against 9.8.
 bool stream_takes(int32_t w, int32_t SBW) {
-    if (w < 24 || (w > 31 && w < 48) || (w > 180 && w < 265) || stream_kind(w) < 0) return false;
+    if (w < 24 || (w > 31 && w < 48) || stream_kind(w) < 0) return false;
     return stream_threads(w, SBW) <= kMaxNT && stream_lds_bytes(w, w, SBW) + kLdsStatic <= kLdsCU;
 }
 
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW) {
     const int G = stream_group(w);
-    return Scratch(G, w, Dims(G, w, stream_threads(wmax, SBW), SBW)).total;
+    const bool H = stream_half(w);
+    return Scratch(G, H, w, Dims(G, H, w, stream_threads(wmax, SBW), SBW)).total;
 }
 
 // Workgroups resident at once: LDS and the registers' waves.

@@ -37,7 +37,7 @@ def series(n, seed):
     return synth.regime_series(n, seed, synth.SHAPES6, len_range=(400, 2500)).x
 
 
-@pytest.mark.parametrize("w", [24, 31, 48, 58, 59, 79, 80, 116, 117, 148, 149, 180, 181, 264, 265, 392, 393, 513, 552])
+@pytest.mark.parametrize("w", [24, 31, 48, 58, 59, 79, 80, 116, 117, 148, 149, 180, 181, 212, 213, 264, 265, 392, 393, 513, 552])
 @pytest.mark.parametrize("l", [7, 150])
 def test_widths(w, l):
     m = w + l - 1
