@@ -60,7 +60,7 @@ struct ProfileJob {
 // handed out by device counters when `counter` is set (kCounters words, zeroed
 // beforehand).
 constexpr int kMaxJobs = 16;
-constexpr int kCounters = 5;
+constexpr int kCounters = 6;
 struct ProfileBatch {
     ProfileJob J[kMaxJobs];
     int64_t tile_end[kMaxJobs];   // job j owns tiles [tile_end[j-1], tile_end[j])
@@ -98,7 +98,7 @@ size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true
 // at once, and the launches, one per kind of kernel the widths need (`share` of
 // the resident workgroups at most, as many as the scratch holds; kind k takes
 // counter[k], zeroed beforehand, when counter is set).
-constexpr int kStreamKinds = 4;
+constexpr int kStreamKinds = 5;
 bool stream_takes(int32_t w, int32_t SBW);
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);
 size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);

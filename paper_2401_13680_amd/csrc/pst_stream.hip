@@ -72,17 +72,21 @@ constexpr int RCH = 6;               // rows per step of a pass
 constexpr int kMaxNT = 448;          // threads of the widest strip
 constexpr int kSelect = 64 * 25;     // listed values that a wave holds in LDS
 constexpr int kSelectPad = 32 * 49;  // read past them, never used
+constexpr int kMaxRank = 16;         // smallest keys that a lane keeps of a block
 constexpr uint32_t kOne = 0x3F800000u;   // key of y = 1, the largest
 constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
 
-// Columns per group: small against w, so that a block's bounds stay tight,
-// while the group minima of a strip leave LDS for the next workgroup.  For w =
+// Columns per group: at most w/2, so that every window holds a whole group, and
+// small against w, so that a block's bounds stay tight, while the group minima
+// of a strip leave LDS for the next workgroup.  For w =
 // 181 .. 264 (strips of 1984 windows, two workgroups a CU) they are kept as
 // their upper 16 bits, rounded down: 24 columns in the space of 48 (w = 257,
 // 100 000 points, l = 256: 11.2 -> 9.3 ms; 200 000 points of a walk: 61 -> 46).
 // Wider strips fill a CU's LDS either way; there whole keys of 48 columns are
 // faster (w = 513: 10.7 against 12.0 ms, half the blocks to bound).
-__host__ __device__ inline int stream_group(int w) { return w < 80 ? 12 : (w <= 264 ? 24 : 48); }
+__host__ __device__ inline int stream_group(int w) {
+    return w < 24 ? 6 : (w < 80 ? 12 : (w <= 264 ? 24 : 48));
+}
 __host__ __device__ inline bool stream_half(int w) { return w > 180 && w <= 264; }
 constexpr int kHalfShift = 14;       // keys are at most kOne = 0x3F800000
 
@@ -106,7 +110,7 @@ struct Dims {
         ldg = half ? 2 * (((NG + 2) / 2) | 1) : (NG + 1) | 1;
         nblk = (SBW + G - 1) / G;          // blocks of G windows
         items = 2 * w + G - 1;             // rows and columns of a block's windows
-        cap = 64 * (half ? 9 : (G == 48 ? 18 : G / 4));   // listed values a wave holds in scratch
+        cap = 64 * (half ? 9 : (G == 48 ? 18 : (G + 3) / 4));   // listed values a wave holds in scratch
     }
 };
 
@@ -292,7 +296,7 @@ __device__ __forceinline__ void row_step(const Cols &c, float (&cov)[V], const f
 template <int G>
 __device__ __forceinline__ uint32_t group_min(const uint32_t (&y)[V]) {
     uint32_t m = min(min(min(y[0], y[1]), y[2]), min(min(y[3], y[4]), y[5]));
-    m = dpp_min<0xB1>(m);                // quad_perm [1,0,3,2]
+    if (G >= 12) m = dpp_min<0xB1>(m);   // quad_perm [1,0,3,2]
     if (G >= 24) m = dpp_min<0x4E>(m);   // quad_perm [2,3,0,1]
     if (G >= 48) m = dpp_min<0x141>(m);  // row_half_mirror
     return m;
@@ -554,6 +558,85 @@ __device__ __forceinline__ void row_keys_of(uint32_t (&U)[NR], uint32_t (&C)[NR]
     else row_keys<T, NR, GC0, 2>(U, C, bm, ldg, w, a, lane, gc, ge);
 }
 
+// a, b in order.
+__device__ __forceinline__ void in_order(uint32_t &a, uint32_t &b) {
+    const uint32_t x = min(a, b);
+    b = max(a, b);
+    a = x;
+}
+__device__ __forceinline__ void sort8(uint32_t (&s)[8]) {
+    constexpr int e[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                              {0, 4}, {3, 7}, {1, 5}, {2, 6}, {1, 4}, {3, 6}, {2, 4}, {3, 5}, {3, 4}};
+#pragma unroll
+    for (int i = 0; i < 19; ++i) in_order(s[e[i][0]], s[e[i][1]]);
+}
+// The K smallest of L and S, both in order, in L.
+template <int K, int N>
+__device__ __forceinline__ void merge_low(uint32_t (&L)[K], const uint32_t (&S)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) L[K - 1 - i] = min(L[K - 1 - i], S[i]);
+#pragma unroll
+    for (int h = K / 2; h >= 1; h /= 2)
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if ((i & h) == 0) in_order(L[i], L[i + h]);
+}
+
+// The k-th smallest U (C: the k-th smallest C), k <= K, of nb blocks from a0 at
+// once: lane b + nb j takes every parts-th row and column of block a0 + b from
+// the j-th on and keeps their K smallest; the parts are merged into lane b.
+// A search by counts (find_from) is a chain of ten ballots for one block after
+// the other, half of a strip's time at w = 33; keeping K keys in order is 9
+// (K = 8) or 14 (K = 16) operations per key with every lane in use: 50 000
+// points, w = 33: 7.6 -> 5.5 ms, w = 65: 3.6 -> 3.0.  With K = 32 (groups of 24
+// columns) the keys no longer fit the registers: 8.5 -> 9.4 ms at w = 129.
+template <int G, int K, bool C>
+__device__ __forceinline__ uint32_t block_ranks(int a0, int nb, int parts, int w, int k, int CS, const Dims &d,
+                                                const uint32_t *bm, const uint32_t *colk, int lane) {
+    const int gc = w / G - 1, ge = 1 + (w - 2) / G - gc;   // as in block_bounds
+    const int part = min(lane / nb, parts - 1), a = a0 + lane % nb;
+    uint32_t L[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) L[i] = part == 0 && i < K - k ? 0u : kNone;
+    for (int x0 = part; x0 < w; x0 += 8 * parts) {
+        uint32_t s[8];
+        int row[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            row[e] = min(x0 + e * parts, w - 1) * d.ldg + a;
+            s[e] = bm[row[e] + 1];
+            if constexpr (!C) s[e] = min(min(min(bm[row[e]], bm[row[e] + gc + 1]), bm[row[e] + gc + ge]), s[e]);
+        }
+        for (int q = 2; q <= gc; ++q)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[e] = min(s[e], bm[row[e] + q]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] = x0 + e * parts < w ? s[e] : kNone;
+        sort8(s);
+        merge_low(L, s);
+    }
+    const int c1 = C ? w : w + G - 1;
+    for (int x0 = part + (C ? G - 1 : 0); x0 < c1; x0 += 8 * parts) {
+        uint32_t s[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int cx = x0 + e * parts, cg = a * G + cx;
+            const bool on = cx < c1 && cg < CS;
+            s[e] = colk[on ? cg : 0];
+            s[e] = on ? s[e] : kNone;
+        }
+        sort8(s);
+        merge_low(L, s);
+    }
+    for (int h = parts / 2; h >= 1; h /= 2) {
+        uint32_t o[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) o[i] = __shfl(L[i], lane + h * nb);
+        merge_low(L, o);
+    }
+    return min(L[K - 1], kOne);
+}
+
 // Bounds and lists of the blocks [a0, a1) of a strip, by one wave; lane + 64 r
 // is row i < w or column x - w of the block's columns.  GC0 .. GC1: the whole
 // groups inside a block's windows (0: any).  H: the keys are the upper halves,
@@ -569,7 +652,50 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
     const int rem = w % G;
     uint32_t U[NR], C[NR];
     uint32_t lo = 0x3D800000u >> SH, hi = lo; // guesses: y = 1/16, then the block before
+    const bool ranked = G <= 12 && k <= kMaxRank;
+    uint32_t los = 0u, his = 0u;
+    int from = a0;
+    // the pieces that this lane's rows need: bit j is group base + j (one atomic
+    // per word and pass over 32 groups instead of three per listed row: w = 33,
+    // 6.6 -> 5.5 ms)
+    uint32_t nm[NR];
+    int base = a0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) nm[r] = 0u;
+    auto flush = [&]() {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int x = lane + 64 * r;
+            if (64 * r < w && x < w) {
+                uint32_t *nd = need + x * d.NGW + (base >> 4);
+                const uint64_t q = (uint64_t)nm[r] << (base & 15);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const uint32_t p = (uint32_t)(q >> (16 * j)) & 0xFFFFu;
+                    if (p) atomicOr(nd + j, p);
+                }
+                nm[r] = 0u;
+            }
+        }
+    };
     for (int a = a0; a < a1; ++a) {
+        if (a - base + w / G + 1 > 31) {
+            flush();
+            base = a;
+        }
+        if constexpr (G <= 12) {
+            if (ranked && (a - a0) % 64 == 0) {
+                from = a;
+                const int nb = min(a1 - a, 64), parts = nb > 32 ? 1 : (nb > 16 ? 2 : (nb > 8 ? 4 : 8));
+                if (k <= 8) {
+                    los = block_ranks<G, 8, false>(a, nb, parts, w, k, CS, d, bm, colk, lane);
+                    his = block_ranks<G, 8, true>(a, nb, parts, w, k, CS, d, bm, colk, lane);
+                } else {
+                    los = block_ranks<G, 16, false>(a, nb, parts, w, k, CS, d, bm, colk, lane);
+                    his = block_ranks<G, 16, true>(a, nb, parts, w, k, CS, d, bm, colk, lane);
+                }
+            }
+        }
         if constexpr (H) row_keys<uint16_t, NR, 0, 0>(U, C, (const uint16_t *)bm, d.ldg, w, a, lane, gc, ge);
         else row_keys_of<uint32_t, NR, GC0, GC1>(U, C, bm, d.ldg, w, a, lane, gc, ge);
 #pragma unroll
@@ -584,16 +710,24 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
             }
         }
     // lo: the k-th smallest U; hi: no less than the k-th smallest C
-        const int span = max((int)(hi - lo), kStep0), step = min(max(span / 8, kStep0), kStep1);
-        lo = find_from<NR>(U, k, (int)lo, step, kStep1, -1, 0, kTop, -1);
-        const int ce = count_le<NR>(C, lo);
-        if (ce >= k || lo >= (uint32_t)kTop) {
-            hi = lo;
+        bool exact;
+        if (G <= 12 && ranked) {
+            lo = (uint32_t)__builtin_amdgcn_readlane((int)los, a - from);
+            hi = (uint32_t)__builtin_amdgcn_readlane((int)his, a - from);
+            exact = lo == hi && lo < (uint32_t)kTop;
         } else {
-            hi = find_from<NR>(C, k, (int)max(hi, lo + (uint32_t)span / 2), step, kStep1, (int)lo, ce, kTop,
-                               2 + (k >> 4));
+            const int span = max((int)(hi - lo), kStep0), step = min(max(span / 8, kStep0), kStep1);
+            lo = find_from<NR>(U, k, (int)lo, step, kStep1, -1, 0, kTop, -1);
+            const int ce = count_le<NR>(C, lo);
+            if (ce >= k || lo >= (uint32_t)kTop) {
+                hi = lo;
+            } else {
+                hi = find_from<NR>(C, k, (int)max(hi, lo + (uint32_t)span / 2), step, kStep1, (int)lo, ce, kTop,
+                                   2 + (k >> 4));
+            }
+            exact = ce >= k;
         }
-        if (!H && ce >= k) {
+        if (!H && exact) {
             if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
             continue;
         }
@@ -601,6 +735,8 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
         int below = 0, n = 0;
         uint2 *la = list + (size_t)a * d.items;
         const int gr = a + w / G;
+        const uint32_t bits = (1u | (gr < d.NG ? 1u << (gr - a) : 0u) |
+                               (rem >= 2 && gr + 1 < d.NG ? 2u << (gr - a) : 0u)) << (a - base);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int x = lane + 64 * r;
@@ -608,6 +744,7 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
             const bool in = !b && U[r] <= hi;
             below += votes(b);
             const uint64_t m = __ballot(in);
+            if (64 * r < w) nm[r] |= in ? bits : 0u;
             if (m == 0) continue;
             if (in) {
                 const int pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -615,18 +752,13 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
                 const bool isrow = x < w;
                 la[pos] = isrow ? make_uint2((uint32_t)x, C[r])
                                 : make_uint2(0x80000000u | (uint32_t)(x - w), colk[a * G + x - w]);
-                if (64 * r < w && isrow) {
-                    uint32_t *nd = need + x * d.NGW;
-                    atomicOr(nd + (a >> 4), 1u << (a & 15));
-                    if (gr < d.NG) atomicOr(nd + (gr >> 4), 1u << (gr & 15));
-                    if (rem >= 2 && gr + 1 < d.NG) atomicOr(nd + ((gr + 1) >> 4), 1u << ((gr + 1) & 15));
-                }
             }
             n += __popcll(m);
         }
         if (lane == 0)
             blk[a] = make_uint4(lo << SH, (hi << SH) | ((1u << SH) - 1u), (uint32_t)below, (uint32_t)n);
     }
+    flush();
 }
 
 // block_bounds with the registers that w needs.
@@ -636,7 +768,9 @@ __device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int C
     const int nr = (d.items + 63) / 64;
 #define BOUNDS(NR, GC0, GC1) block_bounds<G, H, NR, GC0, GC1>(a0, a1, w, k, CS, d, bm, colk, need, blk, list, lane)
     // the widths of each kind: see stream_group and kKindR
-    if constexpr (G == 12) {
+    if constexpr (G == 6) {
+        BOUNDS(1, 1, 2);
+    } else if constexpr (G == 12) {
         if (nr <= 2) BOUNDS(2, 1, 4);
         else BOUNDS(3, 3, 5);
     } else if constexpr (G == 24 && !H) {
@@ -677,9 +811,10 @@ __device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &
         const float *pt = pr + rem - 1;
 #pragma unroll
         for (int p = 0; p < G; p += 4) {
-            const f4 q = *(const f4 *)(pa + p);
+            const f4 q = *(const f4u *)(pa + p);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[p + e] = bits(q[e]);
+            for (int e = 0; e < 4; ++e)
+                if (p + e < G) o[p + e] = bits(q[e]);
         }
         uint32_t run = it.y;
         if constexpr (H) {
@@ -694,16 +829,16 @@ __device__ __forceinline__ void item_values(uint2 it, int a, int w, const Dims &
             }
         }
         for (int x = 0; x < rem - 1; x += 4) {  // columns 0 .. rem-2 (those past it repeat nothing)
-            const f4 q = *(const f4 *)(pr + x);
+            const f4 q = *(const f4u *)(pr + x);
             run = min(run, bits(q[0]));
 #pragma unroll
             for (int e = 1; e < 4; ++e) run = min(run, x + e < rem - 1 ? bits(q[e]) : kNone);
         }
 #pragma unroll
         for (int p = G - 2; p >= 0; --p) o[p] = min(o[p], o[p + 1]);
-        f4 t[G / 4];
+        f4 t[(G + 3) / 4];
 #pragma unroll
-        for (int p = 0; p < G / 4; ++p) t[p] = *(const f4u *)(pt + 4 * p);
+        for (int p = 0; p < (G + 3) / 4; ++p) t[p] = *(const f4u *)(pt + 4 * p);
 #pragma unroll
         for (int p = 0; p < G; ++p) {
             const uint32_t y = p == 0 && rem == 0 ? kNone : bits(t[p / 4][p % 4]);
@@ -959,30 +1094,37 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
         __builtin_amdgcn_wave_barrier();
     };
     // blocks of up to 32 items are taken several at a time, as many as their
-    // items and windows fit the lanes
-    constexpr int LB = G == 12 ? 16 : (G == 24 ? 32 : 64), NB = 64 / LB, ST = G + 1;
+    // windows fit the lanes and their items two (narrow groups) or one a lane
+    constexpr int LB = G < 64 ? G : 64, NB = 64 / LB, ST = G + 1;
+    constexpr int IT = G <= 12 ? 2 : 1, most = 64 * IT * ST <= kSelect ? 64 * IT : kSelect / ST;   // items of a lane, of a wave
     int cnt = 0, T = 0, nmax = 0;
     int mya = 0, myb = 0;   // of the lane's window: its block, the block's first item
-    int ita = 0, itb = 0;   // of the lane's item
+    int ita[IT], itb[IT];   // of the lane's items
+#pragma unroll
+    for (int h = 0; h < IT; ++h) ita[h] = itb[h] = 0;
     for (int a = ab;; ++a) {
         const bool end = a >= ae;
         const uint4 bl = blk[end ? ab : a];
         const int n0 = end ? 0 : uni((int)bl.w);
         const bool few = n0 > 0 && n0 <= 32;
-        if (cnt > 0 && (end || (few && (cnt == NB || T + n0 > 64)))) {
+        if (cnt > 0 && (end || (few && (cnt == NB || T + n0 > most)))) {
             PROBE_MARK(t5);
             PROBE_ADD(8, cnt);
             PROBE_ADD(9, T);
-            if (lane < T) {
-                uint32_t o[G];
-                item_values<G, H>(list[(size_t)ita * d.items + (lane - itb)], ita, w, d, need, pool, gm, o);
 #pragma unroll
-                for (int p = 0; p < G; ++p) lvals[lane * ST + p] = o[p];
+            for (int h = 0; h < IT; ++h) {
+                const int e = lane + 64 * h;
+                if (e < T) {
+                    uint32_t o[G];
+                    item_values<G, H>(list[(size_t)ita[h] * d.items + (e - itb[h])], ita[h], w, d, need, pool, gm, o);
+#pragma unroll
+                    for (int p = 0; p < G; ++p) lvals[e * ST + p] = o[p];
+                }
             }
             wave_sync();
             PROBE_SPAN(6, t5);
             const int p = lane % LB;
-            const bool on = lane / LB < cnt && p < G && p < S.JSe - mya * G;
+            const bool on = lane / LB < cnt && p < S.JSe - mya * G;
             const uint4 mb = blk[mya];
             const int n = on ? (int)mb.w : 0;
             const uint32_t *v = lvals + (on ? myb * ST + p : 0);
@@ -1007,9 +1149,12 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
                 mya = a;
                 myb = T;
             }
-            if (lane >= T) {
-                ita = a;
-                itb = T;
+#pragma unroll
+            for (int h = 0; h < IT; ++h) {
+                if (lane + 64 * h >= T) {
+                    ita[h] = a;
+                    itb[h] = T;
+                }
             }
             ++cnt;
             T += n0;
@@ -1036,7 +1181,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
                     wave_sync();
                 }
             }
-        } else {
+        } else if constexpr (KR > 1) {   // more than 64 need as many keys
             PROBE_ADD(8, 1);
             PROBE_ADD(9, n0);
             PROBE_ADD(10, 1);
@@ -1069,8 +1214,55 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
     PROBE_SPAN(5, t4);
 }
 
-// The jobs of one group width; NT and LDS are sized for the widest of the launch.
-template <int G, bool H, int KR, int WPE>
+// One run of strips of a job, at = its number among the job's.
+template <int G, bool H, int KR>
+__device__ __forceinline__ void do_run(const StreamArgs &A, const ProfileJob &J, int64_t at, float *sm, int NT, int SBW) {
+    const int w = J.w;
+    const int ns = (int)((J.Nm + SBW - 1) / SBW);       // strips of a query
+    const int nrun = (ns + A.run - 1) / A.run;
+    const int first = (int)(at % nrun) * A.run, end = min(first + A.run, ns);
+    uint32_t *carry = (uint32_t *)(sm + Lds(H, w, Dims(G, H, w, NT, SBW)).carry);
+    Strip S;
+    S.J = &J;
+    S.s = (int)(at / nrun);
+    S.in = nullptr;
+    float tmax = 0.0f;
+    // the strip past the run's end, where the run ends inside a tile
+    int i = end < ns && end % A.tile != 0 ? end : end - 1;
+    for (; i >= first; --i) {
+        S.C0 = (int64_t)i * SBW;
+        S.JSe = i < end ? (int)min<int64_t>(SBW, J.Nm - S.C0) : 0;
+        S.CS = S.JSe + w - 1;
+        S.out = carry + (i & 1) * w;
+        __syncthreads();  // the previous strip is done with LDS and the scratch
+        run_strip<G, H, KR>(S, sm, J.rw + (size_t)blockIdx.x * A.B.slot_floats, NT, SBW, tmax);
+        S.in = i % A.tile != 0 ? S.out : nullptr;
+    }
+    if (J.dmax_bits) {  // max of D (the denominator of eq. 18): one atomic per wave
+        float mx = tmax;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        if ((threadIdx.x & 63) == 0) atomicMax(J.dmax_bits, __float_as_uint(mx));
+    }
+}
+
+// Kinds of strip: columns per group, half keys, keys per lane (2w + G - 1 <=
+// 64 KR), waves per SIMD.
+constexpr int kKindG[kStreamKinds] = {6, 12, 24, 24, 48};
+constexpr bool kKindH[kStreamKinds] = {false, false, false, true, false};
+constexpr int kKindR[kStreamKinds] = {1, 3, 6, 9, 18};
+constexpr int kKindW[kStreamKinds] = {3, 3, 3, 4, 2};
+constexpr int kNarrow = 3;   // the first kinds, alike in what a CU holds of them
+__host__ __device__ inline int stream_kind(int w) {
+    constexpr int g[kStreamKinds] = {6, 12, 24, 24, 48}, r[kStreamKinds] = {1, 3, 6, 9, 18};
+    constexpr bool h[kStreamKinds] = {false, false, false, true, false};
+    for (int k = 0; k < kStreamKinds; ++k)
+        if (g[k] == stream_group(w) && h[k] == stream_half(w) && 2 * w + g[k] - 1 <= 64 * r[k]) return k;
+    return -1;
+}
+
+// Jobs of the kinds K0 .. K1; NT and LDS are sized for the widest of the launch.
+template <int K0, int K1, int WPE>
 __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE))) k_stream(StreamArgs A) {
     extern __shared__ __align__(16) float sm[];
     __shared__ uint32_t next_run;
@@ -1087,33 +1279,17 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
         while (jb + 1 < A.B.njobs && gt >= A.B.tile_end[jb]) ++jb;
         const ProfileJob &J = A.B.J[jb];
         const int64_t at = gt - (jb > 0 ? A.B.tile_end[jb - 1] : 0);
-        const int w = J.w;
-        const int ns = (int)((J.Nm + SBW - 1) / SBW);       // strips of a query
-        const int nrun = (ns + A.run - 1) / A.run;
-        const int first = (int)(at % nrun) * A.run, end = min(first + A.run, ns);
-        uint32_t *carry = (uint32_t *)(sm + Lds(H, w, Dims(G, H, w, NT, SBW)).carry);
-        Strip S;
-        S.J = &J;
-        S.s = (int)(at / nrun);
-        S.in = nullptr;
-        float tmax = 0.0f;
-        // the strip past the run's end, where the run ends inside a tile
-        int i = end < ns && end % A.tile != 0 ? end : end - 1;
-        for (; i >= first; --i) {
-            S.C0 = (int64_t)i * SBW;
-            S.JSe = i < end ? (int)min<int64_t>(SBW, J.Nm - S.C0) : 0;
-            S.CS = S.JSe + w - 1;
-            S.out = carry + (i & 1) * w;
-            __syncthreads();  // the previous strip is done with LDS and the scratch
-            run_strip<G, H, KR>(S, sm, J.rw + (size_t)blockIdx.x * A.B.slot_floats, NT, SBW, tmax);
-            S.in = i % A.tile != 0 ? S.out : nullptr;
-        }
-        if (J.dmax_bits) {  // max of D (the denominator of eq. 18): one atomic per wave
-            float mx = tmax;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-            if ((threadIdx.x & 63) == 0) atomicMax(J.dmax_bits, __float_as_uint(mx));
-        }
+        const int kind = K0 == K1 ? K0 : stream_kind(J.w);
+        if constexpr (K0 == 0)
+            if (kind == 0) do_run<kKindG[0], kKindH[0], kKindR[0]>(A, J, at, sm, NT, SBW);
+        if constexpr (K0 <= 1 && K1 >= 1)
+            if (kind == 1) do_run<kKindG[1], kKindH[1], kKindR[1]>(A, J, at, sm, NT, SBW);
+        if constexpr (K0 <= 2 && K1 >= 2)
+            if (kind == 2) do_run<kKindG[2], kKindH[2], kKindR[2]>(A, J, at, sm, NT, SBW);
+        if constexpr (K0 <= 3 && K1 >= 3)
+            if (kind == 3) do_run<kKindG[3], kKindH[3], kKindR[3]>(A, J, at, sm, NT, SBW);
+        if constexpr (K1 == 4)
+            if (kind == 4) do_run<kKindG[4], kKindH[4], kKindR[4]>(A, J, at, sm, NT, SBW);
         if (A.B.counter) {
             __syncthreads();
             if (threadIdx.x == 0) next_run = atomicAdd(A.B.counter, 1u);
@@ -1125,23 +1301,10 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
     }
 }
 
-// Kinds of kernel: columns per group, half keys, keys per lane (2w + G - 1 <=
-// 64 KR), waves per SIMD.
-constexpr int kKindG[kStreamKinds] = {12, 24, 24, 48};
-constexpr bool kKindH[kStreamKinds] = {false, false, true, false};
-constexpr int kKindR[kStreamKinds] = {3, 6, 9, 18};
-constexpr int kKindW[kStreamKinds] = {3, 3, 4, 2};
-const void *const kKernels[kStreamKinds] = {
-    (const void *)k_stream<kKindG[0], kKindH[0], kKindR[0], kKindW[0]>,
-    (const void *)k_stream<kKindG[1], kKindH[1], kKindR[1], kKindW[1]>,
-    (const void *)k_stream<kKindG[2], kKindH[2], kKindR[2], kKindW[2]>,
-    (const void *)k_stream<kKindG[3], kKindH[3], kKindR[3], kKindW[3]>};
-int stream_kind(int w) {
-    for (int k = 0; k < kStreamKinds; ++k)
-        if (kKindG[k] == stream_group(w) && kKindH[k] == stream_half(w) && 2 * w + kKindG[k] - 1 <= 64 * kKindR[k])
-            return k;
-    return -1;
-}
+const void *const kKernels[kStreamKinds + 1] = {
+    (const void *)k_stream<0, 0, kKindW[0]>, (const void *)k_stream<1, 1, kKindW[1]>,
+    (const void *)k_stream<2, 2, kKindW[2]>, (const void *)k_stream<3, 3, kKindW[3]>,
+    (const void *)k_stream<4, 4, kKindW[4]>, (const void *)k_stream<0, kNarrow - 1, kKindW[0]>};
 
 constexpr int64_t kRunsPerSlot = 6;
 constexpr size_t kLdsCU = 160 * 1024;
@@ -1160,13 +1323,14 @@ size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW) {
     return 4 * (size_t)Lds(H, w, Dims(stream_group(w), H, w, stream_threads(wmax, SBW), SBW)).total;
 }
 
-// Where k_profile is the better one (ms, 50 000 points, l = m/2, k_profile
-// against this kernel, regime series / random walk): short windows, w = 33:
-// 6.4 / 5.7 against 7.6 / 7.8, w = 41: 5.7 / 5.3 against 5.9 / 6.1; w = 49: 5.0
-// / 5.2 against 4.3 / 4.9.  Below w = 32 k_profile scans each window: w = 26:
-// 16.8 against 9.8.
+// k_profile keeps the windows that hold no two groups of six columns.  Above it
+// is never the better one (ms, l = m/2, k_profile against this kernel; 50 000
+// points of a regime series / a random walk): w = 12: 14.6 / 14.3 against 8.7 /
+// 8.6, w = 17: 16.2 / 16.0 against 7.7 / 7.7, w = 24: 14.0 / 13.8 against 5.5 /
+// 5.4, w = 33: 6.4 / 5.7 against 4.9 / 5.1, w = 65: 4.2 / 4.7 against 2.9 / 3.8;
+// 5 000 points: w = 12: 0.51 against 0.20, w = 33: 0.45 against 0.13.
 bool stream_takes(int32_t w, int32_t SBW) {
-    if (w < 24 || (w > 31 && w < 48) || stream_kind(w) < 0) return false;
+    if (w < 12 || stream_kind(w) < 0) return false;
     return stream_threads(w, SBW) <= kMaxNT && stream_lds_bytes(w, w, SBW) + kLdsStatic <= kLdsCU;
 }
 
@@ -1196,48 +1360,63 @@ hipError_t stream_prepare() {
 hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
                          double share, uint32_t *counter, hipStream_t st) {
     if (n < 1 || n > kMaxJobs) return hipErrorInvalidValue;
-    int32_t ws[kMaxJobs];
+    int kinds = 0;
     for (int i = 0; i < n; ++i) {
-        ws[i] = jobs[i].w;
-        if (!stream_takes(ws[i], SBW)) return hipErrorInvalidValue;
+        if (!stream_takes(jobs[i].w, SBW)) return hipErrorInvalidValue;
+        kinds |= 1 << stream_kind(jobs[i].w);
     }
-    // one launch per group width among the jobs, widest first
+    // One launch per kind among the jobs, widest first.  The narrow kinds share
+    // one: each launch ends with a strip's latency on a chip that empties (lengths
+    // 64, 80 .. 176, 5 000 points, w = 33 .. 89: 1.5 ms in two, 0.9 in one).  The
+    // wider ones hold other numbers of waves: all kinds in one kernel at two waves
+    // per SIMD take 7.0 ms where separate launches take 5.2 (96, 128 .. 320,
+    // 20 000 points).
+    const int narrow = kinds & ((1 << kNarrow) - 1);
+    const bool mixed = (narrow & (narrow - 1)) != 0;
     for (int kind = kStreamKinds - 1; kind >= 0; --kind) {
+        const bool all = mixed && kind == kNarrow - 1;
+        const int set = all ? narrow : (mixed && kind < kNarrow ? 0 : kinds & 1 << kind);
+        if (set == 0) continue;
         StreamArgs a;
         a.SBW = SBW;
         a.B.njobs = 0;
         a.B.counter = counter ? counter + kind : nullptr;
         a.B.slot_floats = 0;
         int32_t wmax = 0;
-        for (int i = 0; i < n; ++i)
-            if (stream_kind(ws[i]) == kind) wmax = std::max(wmax, ws[i]);
-        if (wmax == 0) continue;
-        const int64_t most = std::max<int64_t>(1, (int64_t)(share * stream_slots(wmax, SBW)));
-        // runs as long as leave every workgroup several of them
         int64_t strips = 0;
         for (int i = 0; i < n; ++i)
-            if (stream_kind(ws[i]) == kind) strips += ((jobs[i].Nm + SBW - 1) / SBW) * (int64_t)jobs[i].nq;
+            if (set >> stream_kind(jobs[i].w) & 1) {
+                wmax = std::max(wmax, jobs[i].w);
+                strips += ((jobs[i].Nm + SBW - 1) / SBW) * (int64_t)jobs[i].nq;
+            }
+        size_t lds = 0;
+        for (int i = 0; i < n; ++i)
+            if (set >> stream_kind(jobs[i].w) & 1) {
+                a.B.slot_floats = std::max(a.B.slot_floats, stream_slot_floats(jobs[i].w, wmax, SBW));
+                lds = std::max(lds, stream_lds_bytes(jobs[i].w, wmax, SBW));
+            }
+        if (lds + kLdsStatic > kLdsCU) return hipErrorInvalidValue;
+        const int64_t most = std::max<int64_t>(1, (int64_t)(share * stream_slots(wmax, SBW)));
+        // runs as long as leave every workgroup several of them
         a.tile = tile;
         a.run = tile;
         while (a.run > 1 && (a.run % 2 != 0 || strips < kRunsPerSlot * most * a.run)) a.run = a.run % 2 ? 1 : a.run / 2;
-        size_t lds = 0;
         int64_t acc = 0;
-        for (int i = 0; i < n; ++i) {
-            if (stream_kind(ws[i]) != kind) continue;
-            const int j = a.B.njobs++;
-            a.B.J[j] = jobs[i];
-            const int64_t ns = (jobs[i].Nm + SBW - 1) / SBW;
-            acc += ((ns + a.run - 1) / a.run) * (int64_t)jobs[i].nq;
-            a.B.tile_end[j] = acc;
-            a.B.slot_floats = std::max(a.B.slot_floats, stream_slot_floats(ws[i], wmax, SBW));
-            lds = std::max(lds, stream_lds_bytes(ws[i], wmax, SBW));
-        }
+        for (int k = kStreamKinds - 1; k >= 0; --k)
+            for (int i = 0; i < n; ++i) {
+                if (stream_kind(jobs[i].w) != k || !(set >> k & 1)) continue;
+                const int j = a.B.njobs++;
+                a.B.J[j] = jobs[i];
+                const int64_t ns = (jobs[i].Nm + SBW - 1) / SBW;
+                acc += ((ns + a.run - 1) / a.run) * (int64_t)jobs[i].nq;
+                a.B.tile_end[j] = acc;
+            }
         const int64_t fit = (int64_t)(scratch_floats / a.B.slot_floats);
         const int64_t grid = std::min(std::min(acc, fit), most);
-        if (grid < 1 || lds + kLdsStatic > kLdsCU) return hipErrorInvalidValue;
+        if (grid < 1) return hipErrorInvalidValue;
         void *args[] = {&a};
-        const hipError_t e = hipLaunchKernel(kKernels[kind], dim3((unsigned)grid), dim3(stream_threads(wmax, SBW)),
-                                             args, lds, st);
+        const hipError_t e = hipLaunchKernel(kKernels[all ? kStreamKinds : kind], dim3((unsigned)grid),
+                                             dim3(stream_threads(wmax, SBW)), args, lds, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -99,3 +99,24 @@ def test_batch_of_both_kernels_equals_each_alone():
     X = torch.from_numpy(np.stack([series(5000, 42 + j) for j in range(3)])).cuda()
     a, b = both(lambda c: api.snippets_multi(X, 256, 128, 3, ctx=c))
     assert a == b
+
+
+@pytest.mark.parametrize("w", [12, 13, 17, 18, 23, 24, 29, 35, 36, 47, 79])
+@pytest.mark.parametrize("k", [0, 1, 8, 9, 16, 17, 10 ** 6])
+def test_narrow_widths(w, k):
+    """Groups of 6 and 12 columns, k at the edges of the lists that a lane keeps."""
+    l = 29
+    m = w + l - 1
+    k = min(k, 2 * w + 3)
+    same_set(series(5 * m + 2100, w + k), m, l, k)
+    x = series(2 * m + 1200, w)
+    x[m:3 * m // 2] = 1.5
+    x[500:] = np.tile(x[500:540], len(x) // 40 + 1)[:len(x) - 500]
+    same_set(x, m, l, k)
+
+
+@pytest.mark.parametrize("ms", [[30, 64], [30, 50, 100, 200], [64, 200, 330], [30, 300, 500, 900]])
+def test_narrow_kinds_share_a_launch(ms):
+    T = torch.from_numpy(series(4100, 43)).cuda()
+    ref, got = both(lambda c: api.select_length(T, ms, 3, ctx=c))
+    assert ref == got
