@@ -120,3 +120,16 @@ def test_narrow_kinds_share_a_launch(ms):
     T = torch.from_numpy(series(4100, 43)).cuda()
     ref, got = both(lambda c: api.select_length(T, ms, 3, ctx=c))
     assert ref == got
+
+
+@pytest.mark.parametrize("w", [80, 129, 180])
+@pytest.mark.parametrize("k", ["1", "31", "33", "w", "2w-33", "2w-31", "2w"])
+def test_long_lists(w, k):
+    """Ranks on both sides of the keys that a lane keeps of a long list, from
+    either end, on series whose blocks list most of their rows."""
+    k = {"1": 1, "31": 31, "33": 33, "w": w, "2w-33": 2 * w - 33, "2w-31": 2 * w - 31, "2w": 2 * w}[k]
+    rng = np.random.default_rng(w + k)
+    m = 2 * w - 2
+    n = 3 * m + 1400
+    same_set(np.cumsum(rng.normal(size=n)), m, w - 1, k)
+    same_set(rng.normal(size=n), m, w - 1, k)
