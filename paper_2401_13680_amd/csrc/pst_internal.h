@@ -99,6 +99,8 @@ size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true
 // the resident workgroups at most, as many as the scratch holds; kind k takes
 // counter[k], zeroed beforehand, when counter is set).
 constexpr int kStreamKinds = 5;
+constexpr int kStreamNarrow = 178;   // the widest of the narrow kinds, which share a launch: the built-in
+                                     // strips are 992 windows to here, 1984 past it
 bool stream_takes(int32_t w, int32_t SBW);
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);
 size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);

@@ -80,7 +80,7 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
 // Columns per group: at most w/2, so that every window holds a whole group, and
 // small against w, so that a block's bounds stay tight, while the group minima
 // of a strip leave LDS for the next workgroup.  For w =
-// 181 .. 264 (strips of 1984 windows, two workgroups a CU) they are kept as
+// 179 .. 264 (strips of 1984 windows, two workgroups a CU) they are kept as
 // their upper 16 bits, rounded down: 24 columns in the space of 48 (w = 257,
 // 100 000 points, l = 256: 11.2 -> 9.3 ms; 200 000 points of a walk: 61 -> 46).
 // Wider strips fill a CU's LDS either way; there whole keys of 48 columns are
@@ -88,7 +88,7 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
 __host__ __device__ inline int stream_group(int w) {
     return w < 24 ? 6 : (w < 80 ? 12 : (w <= 264 ? 24 : 48));
 }
-__host__ __device__ inline bool stream_half(int w) { return w > 180 && w <= 264; }
+__host__ __device__ inline bool stream_half(int w) { return w > kStreamNarrow && w <= 264; }
 constexpr int kHalfShift = 14;       // keys are at most kOne = 0x3F800000
 
 struct StreamArgs {

@@ -93,9 +93,8 @@ def test_batch_of_both_kernels_equals_each_alone():
     ms = [50, 64, 70, 128, 200, 330, 420, 600]
     ref, got = both(lambda c: api.select_length(T, ms, 3, ctx=c))
     assert ref == got
-    one = api.select_length(T, ms, 3, one_launch=True, graph=False)
-    ref1, got1 = both(lambda c: api.select_length(T, ms, 3, one_launch=True, graph=False, ctx=c))
-    assert ref1 == got1 == one
+    # in one launch every length keeps the strips it has in a launch of its own
+    assert api.select_length(T, ms, 3, one_launch=True, graph=False) == got
     X = torch.from_numpy(np.stack([series(5000, 42 + j) for j in range(3)])).cuda()
     a, b = both(lambda c: api.snippets_multi(X, 256, 128, 3, ctx=c))
     assert a == b
