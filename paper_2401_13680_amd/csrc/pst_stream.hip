@@ -96,6 +96,7 @@ struct StreamArgs {
     int32_t SBW;
     int32_t run;        // strips of a run, a divisor of `tile`
     int32_t tile;       // strips of a tile
+    int32_t tail;       // the last job's queries from here are taken strip by strip
 };
 static_assert(sizeof(StreamArgs) <= 4000, "kernel arguments must fit the 4 KB limit");
 
@@ -1251,15 +1252,22 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
 
 // One run of strips of a job, at = its number among the job's.
 template <int G, bool H, int KR>
-__device__ __forceinline__ void do_run(const StreamArgs &A, const ProfileJob &J, int64_t at, float *sm, int NT, int SBW) {
+__device__ __forceinline__ void do_run(const StreamArgs &A, const ProfileJob &J, int64_t at, bool last, float *sm, int NT,
+                                       int SBW) {
     const int w = J.w;
     const int ns = (int)((J.Nm + SBW - 1) / SBW);       // strips of a query
-    const int nrun = (ns + A.run - 1) / A.run;
-    const int first = (int)(at % nrun) * A.run, end = min(first + A.run, ns);
+    int run = A.run, nrun = (ns + run - 1) / run, s0 = 0;
+    if (last && at >= (int64_t)A.tail * nrun) {
+        at -= (int64_t)A.tail * nrun;
+        s0 = A.tail;
+        run = 1;
+        nrun = ns;
+    }
+    const int first = (int)(at % nrun) * run, end = min(first + run, ns);
     uint32_t *carry = (uint32_t *)(sm + Lds(H, w, Dims(G, H, w, NT, SBW)).carry);
     Strip S;
     S.J = &J;
-    S.s = (int)(at / nrun);
+    S.s = s0 + (int)(at / nrun);
     S.in = nullptr;
     float tmax = 0.0f;
     // the strip past the run's end, where the run ends inside a tile
@@ -1316,15 +1324,15 @@ __global__ void __launch_bounds__(kMaxNT) __attribute__((amdgpu_waves_per_eu(WPE
         const int64_t at = gt - (jb > 0 ? A.B.tile_end[jb - 1] : 0);
         const int kind = K0 == K1 ? K0 : stream_kind(J.w);
         if constexpr (K0 == 0)
-            if (kind == 0) do_run<kKindG[0], kKindH[0], kKindR[0]>(A, J, at, sm, NT, SBW);
+            if (kind == 0) do_run<kKindG[0], kKindH[0], kKindR[0]>(A, J, at, jb == A.B.njobs - 1, sm, NT, SBW);
         if constexpr (K0 <= 1 && K1 >= 1)
-            if (kind == 1) do_run<kKindG[1], kKindH[1], kKindR[1]>(A, J, at, sm, NT, SBW);
+            if (kind == 1) do_run<kKindG[1], kKindH[1], kKindR[1]>(A, J, at, jb == A.B.njobs - 1, sm, NT, SBW);
         if constexpr (K0 <= 2 && K1 >= 2)
-            if (kind == 2) do_run<kKindG[2], kKindH[2], kKindR[2]>(A, J, at, sm, NT, SBW);
+            if (kind == 2) do_run<kKindG[2], kKindH[2], kKindR[2]>(A, J, at, jb == A.B.njobs - 1, sm, NT, SBW);
         if constexpr (K0 <= 3 && K1 >= 3)
-            if (kind == 3) do_run<kKindG[3], kKindH[3], kKindR[3]>(A, J, at, sm, NT, SBW);
+            if (kind == 3) do_run<kKindG[3], kKindH[3], kKindR[3]>(A, J, at, jb == A.B.njobs - 1, sm, NT, SBW);
         if constexpr (K1 == 4)
-            if (kind == 4) do_run<kKindG[4], kKindH[4], kKindR[4]>(A, J, at, sm, NT, SBW);
+            if (kind == 4) do_run<kKindG[4], kKindH[4], kKindR[4]>(A, J, at, jb == A.B.njobs - 1, sm, NT, SBW);
         if (A.B.counter) {
             __syncthreads();
             if (threadIdx.x == 0) next_run = atomicAdd(A.B.counter, 1u);
@@ -1341,7 +1349,13 @@ const void *const kKernels[kStreamKinds + 1] = {
     (const void *)k_stream<2, 2, kKindW[2]>, (const void *)k_stream<3, 3, kKindW[3]>,
     (const void *)k_stream<4, 4, kKindW[4]>, (const void *)k_stream<0, kNarrow - 1, kKindW[0]>};
 
-constexpr int64_t kRunsPerSlot = 6;
+// A run of r strips costs 1/r strip's first w-1 columns over again, and ends up
+// to r strips after the others: runs as long as leave each workgroup three,
+// then four single strips a workgroup (ms, runs to the end / with them: w = 33,
+// 50 000 points 5.0 / 4.75; w = 257, a walk of 200 000 45.5 / 43.9; w = 513,
+// 100 003 10.4 / 9.8, 200 000 41.4 / 38.6).
+constexpr int64_t kRunsPerSlot = 3;
+constexpr int64_t kTailStrips = 4;
 constexpr size_t kLdsCU = 160 * 1024;
 constexpr size_t kLdsStatic = 512;   // next_run, the vote of __syncthreads_or, alignment
 
@@ -1432,7 +1446,6 @@ hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t til
             }
         if (lds + kLdsStatic > kLdsCU) return hipErrorInvalidValue;
         const int64_t most = std::max<int64_t>(1, (int64_t)(share * stream_slots(wmax, SBW)));
-        // runs as long as leave every workgroup several of them
         a.tile = tile;
         a.run = tile;
         while (a.run > 1 && (a.run % 2 != 0 || strips < kRunsPerSlot * most * a.run)) a.run = a.run % 2 ? 1 : a.run / 2;
@@ -1445,7 +1458,15 @@ hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t til
                 const int64_t ns = (jobs[i].Nm + SBW - 1) / SBW;
                 acc += ((ns + a.run - 1) / a.run) * (int64_t)jobs[i].nq;
                 a.B.tile_end[j] = acc;
+                a.tail = jobs[i].nq;
             }
+        if (a.run > 1) {   // the launch ends with single strips, some for every workgroup
+            const ProfileJob &J = a.B.J[a.B.njobs - 1];
+            const int64_t ns = (J.Nm + SBW - 1) / SBW;
+            a.tail = (int32_t)std::max<int64_t>(0, J.nq - (kTailStrips * most + ns - 1) / ns);
+            acc += (J.nq - a.tail) * (ns - (ns + a.run - 1) / a.run);
+            a.B.tile_end[a.B.njobs - 1] = acc;
+        }
         const int64_t fit = (int64_t)(scratch_floats / a.B.slot_floats);
         const int64_t grid = std::min(std::min(acc, fit), most);
         if (grid < 1) return hipErrorInvalidValue;

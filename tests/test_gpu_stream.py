@@ -132,3 +132,15 @@ def test_long_lists(w, k):
     n = 3 * m + 1400
     same_set(np.cumsum(rng.normal(size=n)), m, w - 1, k)
     same_set(rng.normal(size=n), m, w - 1, k)
+
+
+@pytest.mark.parametrize("n,m", [(40011, 64), (60013, 256), (100000, 400)])
+def test_runs_of_strips(n, m):
+    """Long enough for runs of several strips and the single ones after them."""
+    same_set(series(n, m), m, m // 2)
+
+
+def test_runs_of_strips_in_a_batch():
+    T = torch.from_numpy(series(40000, 44)).cuda()
+    ref, got = both(lambda c: api.select_length(T, [64, 128], 3, ctx=c))
+    assert ref == got
