@@ -95,6 +95,7 @@ PROBE_NAMES = {0: "windows", 1: "run_starts", 2: "windows_by_own_pass", 3: "coop
                4: "misses_below", 5: "misses_above", 6: "list_overflows", 7: "misses_at_run_start",
                8: "overflows_of_one_key_brackets", 9: "sum_of_list_lengths", 10: "overflows_holding_kth",
                11: "second_pass_brackets", 12: "windows_by_second_pass"}
+STREAM_PHASES = {0: "set-up and anchors", 1: "first pass", 3: "bounds", 4: "second pass", 5: "selection"}
 PROBE_PHASES = {16: "distance phase", 17: "  FP64 anchors", 18: "  FP32 recurrence", 19: "  column minima",
                 20: "  sliding row minima", 21: "selection phase", 22: "  run starts (radix select)",
                 23: "  bracket passes", 24: "  sorts and second passes", 25: "  cooperative selects"}
@@ -123,11 +124,23 @@ def probe_bench(args):
         api.set_geometry(m - l + 1, int(args.probe_geometry, 0))
     api.profile_set(T, m, l)
     torch.cuda.synchronize()
+    L.pst_stream_probe_read.argtypes = [ctypes.POINTER(ctypes.c_ulonglong), ctypes.c_int]
+    sbuf = (ctypes.c_ulonglong * 16)()
     L.pst_probe_read(buf, 1)
+    L.pst_stream_probe_read(sbuf, 1)
     api.profile_set(T, m, l)
     torch.cuda.synchronize()
     L.pst_probe_read(buf, 1)
+    L.pst_stream_probe_read(sbuf, 1)
     tot = buf[16] + buf[21]
+    stot = sum(sbuf[k] for k in STREAM_PHASES)
+    if stot:  # the streaming kernel ran it
+        print(json.dumps(dict(workload=WORKLOAD["name"], m=m, l=l, kernel="k_stream",
+                              counts=dict(blocks=int(sbuf[8]), listed=int(sbuf[9]), long_lists=int(sbuf[10])),
+                              wave_cycles={v: int(sbuf[k]) for k, v in STREAM_PHASES.items()},
+                              share_of_wave_time={v: round(sbuf[k] / stot, 4) for k, v in STREAM_PHASES.items()})),
+              flush=True)
+        return
     out = dict(workload=WORKLOAD["name"], m=m, l=l, geometry=hex(api.geometry(m - l + 1)), counts={v: int(buf[k]) for k, v in PROBE_NAMES.items()},
                wave_cycles={v.strip(): int(buf[k]) for k, v in PROBE_PHASES.items()},
                share_of_wave_time={v.strip(): round(buf[k] / tot, 4) for k, v in PROBE_PHASES.items()})
@@ -587,7 +600,7 @@ def serve_bench(args):
                host_submit_pcie_inclusive=dict(value=cells / host_sat, seconds=host_sat),
                roofline=dict(bound="alu", achieved=achieved, peak=peak, unit="Tops/s (VALU lane-ops)",
                              frac=achieved / peak, traffic=measured_traffic(cells_per_launch=cells / nreq),
-                             kernel="k_profile", kernel_ms=k_ms / nreq, launches=nreq,
+                             kernel="k_stream, k_profile", kernel_ms=k_ms / nreq, launches=nreq,
                              ops_per_cell=OPS_PER_CELL,
                              note="profile launches of the plain pass over the same requests, "
                                   "HIP events around each launch"),
@@ -724,7 +737,7 @@ def main():
                     step="stats + all segment profiles + greedy + neighbours"),
         latency_ms=dict(p50=float(np.percentile(lat, 50)), p99=float(np.percentile(lat, 99))),
         roofline=dict(bound="alu", achieved=achieved, peak=peak, unit="Tops/s (VALU lane-ops)",
-                      frac=achieved / peak, traffic=measured_traffic(cells, "hbm bytes per cell at m=256"), kernel="k_profile",
+                      frac=achieved / peak, traffic=measured_traffic(cells, "hbm bytes per cell at m=256"), kernel="k_stream",
                       kernel_ms=k_ms, ops_per_cell=OPS_PER_CELL),
     )
     if args.calibrate_copy:

@@ -105,8 +105,8 @@ int pst_mpdist_profile(pst_ctx *ctx, const double *T_dev, int64_t n,
  * library runs on, held until the process ends; the call allocates nothing.
  * The statistics of T take 64 bytes per point (n up to about 4 million at
  * m = 256, l = 128); the persistent grid shrinks to the profile slots that
- * fit in the rest (4 MB each at that m and l), so long series run on fewer
- * compute units.  Results equal pst_mpdist_profile's.
+ * fit in the rest (0.8 MB each at that m and l; 4 MB where the tiled kernel
+ * runs), so long series run on fewer compute units.  Results equal pst_mpdist_profile's.
  * Every call on one GPU uses the same array: calls that overlap on one GPU
  * (other threads, contexts or streams) race and must be serialised by the
  * caller.  The call returns once its work is done.  PST_EINVAL as
@@ -378,7 +378,8 @@ int pst_label_f1(pst_ctx *ctx, const int32_t *owner_dev, int64_t n, int32_t m, i
  *                          [0, 1]; results stay within the profile tolerance
  *                          of the built-in geometry, not bit for bit
  *   PST_OPT_SWEEP_ONE_LAUNCH  run every length of a batched sweep in one
- *                          launch with the widest length's tile geometry [0, 1]
+ *                          batch with the widest length's tile geometry [0, 1];
+ *                          lengths of at most 178 windows keep the built-in one
  *                          (0: one launch per workgroup shape among the
  *                          lengths); results within the profile tolerance
  *   PST_OPT_ANCHOR_EVERY   R > 0: besides the FP64 anchor at the first cell of
