@@ -82,15 +82,26 @@ __global__ void __launch_bounds__(kT) k_reduce_part(const double *__restrict__ x
     }
 }
 
-__global__ void k_reduce_final(const double *__restrict__ part, int np, int64_t n,
-                               double *__restrict__ misc) {
-    if (threadIdx.x != 0) return;
+// The partials are staged in LDS: one thread adds them in order, and from
+// global memory each addition waited for its own loads (10^6 points: 34 -> 7 us).
+__global__ void __launch_bounds__(kT) k_reduce_final(const double *__restrict__ part, int np, int64_t n,
+                                                     double *__restrict__ misc) {
+    __shared__ double sp[3 * kT];
     double s = 0.0, mx = 0.0, bad = 0.0;
-    for (int i = 0; i < np; ++i) {
-        s += part[3 * i];
-        mx = fmax(mx, part[3 * i + 1]);
-        bad = fmax(bad, part[3 * i + 2]);
+    for (int i0 = 0; i0 < np; i0 += kT) {
+        const int c = min(kT, np - i0);
+        for (int i = threadIdx.x; i < 3 * c; i += kT) sp[i] = part[3 * i0 + i];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int i = 0; i < c; ++i) {
+                s += sp[3 * i];
+                mx = fmax(mx, sp[3 * i + 1]);
+                bad = fmax(bad, sp[3 * i + 2]);
+            }
+        }
+        __syncthreads();
     }
+    if (threadIdx.x != 0) return;
     misc[0] = bad != 0.0 ? 0.0 : s / (double)n;
     misc[1] = mx;
     misc[2] = bad;
@@ -136,18 +147,30 @@ __global__ void __launch_bounds__(kT) k_center_block(const double *__restrict__ 
         for (int c = 0; c < 4; ++c) blk[4 * blockIdx.x + c] = sh[c][0];
 }
 
-// Exclusive scan of the block sums (sequential; a few hundred blocks at most).
-__global__ void k_scan_blocks(double *__restrict__ blk, int nb) {
-    if (threadIdx.x != 0) return;
+// Exclusive scan of the block sums: sequential (a few hundred blocks at most),
+// in LDS.  In global memory each step waited for the loads behind its own
+// stores (10^6 points: 41 -> 21 us).
+__global__ void __launch_bounds__(kT) k_scan_blocks(double *__restrict__ blk, int nb) {
+    __shared__ double sb[4 * kT];
     dd s{0.0, 0.0}, q{0.0, 0.0};
-    for (int b = 0; b < nb; ++b) {
-        dd bs{blk[4 * b], blk[4 * b + 1]}, bq{blk[4 * b + 2], blk[4 * b + 3]};
-        blk[4 * b + 0] = s.hi;
-        blk[4 * b + 1] = s.lo;
-        blk[4 * b + 2] = q.hi;
-        blk[4 * b + 3] = q.lo;
-        s = dd_add(s, bs);
-        q = dd_add(q, bq);
+    for (int b0 = 0; b0 < nb; b0 += kT) {
+        const int c = min(kT, nb - b0);
+        for (int i = threadIdx.x; i < 4 * c; i += kT) sb[i] = blk[4 * (int64_t)b0 + i];
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int b = 0; b < c; ++b) {
+                dd bs{sb[4 * b], sb[4 * b + 1]}, bq{sb[4 * b + 2], sb[4 * b + 3]};
+                sb[4 * b + 0] = s.hi;
+                sb[4 * b + 1] = s.lo;
+                sb[4 * b + 2] = q.hi;
+                sb[4 * b + 3] = q.lo;
+                s = dd_add(s, bs);
+                q = dd_add(q, bq);
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 4 * c; i += kT) blk[4 * (int64_t)b0 + i] = sb[i];
+        __syncthreads();
     }
 }
 
@@ -310,9 +333,9 @@ hipError_t launch_series_stats(const double *x, char *base, const StatsLayout &L
     int np = (int)std::min<int64_t>(1024, (n + kT * 16 - 1) / (kT * 16));
     if (np < 1) np = 1;
     hipLaunchKernelGGL(k_reduce_part, dim3(np), dim3(kT), 0, st, x, n, part);
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(64), 0, st, part, np, n, misc);
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kT), 0, st, part, np, n, misc);
     hipLaunchKernelGGL(k_center_block, dim3(L.nblk), dim3(kT), 0, st, x, n, misc, xc, blk);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(64), 0, st, blk, L.nblk);
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kT), 0, st, blk, L.nblk);
     hipLaunchKernelGGL(k_prefix, dim3(L.nblk), dim3(kT), 0, st, xc, n, blk, pre);
     int nw = (int)std::min<int64_t>(4096, (L.Nl + kStatsPad + kT - 1) / kT);
     if (nw < 1) nw = 1;
