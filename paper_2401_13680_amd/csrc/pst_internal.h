@@ -93,7 +93,8 @@ bool profile_set_geometry(int32_t w, int32_t code);
 size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true);
 
 // The streaming profile kernel (pst_stream.hip): whether it runs jobs of
-// width w in strips of SBW windows (`tile` of them to a tile), a workgroup's scratch and LDS for
+// width w in strips of SBW windows (`tile` of them to a tile), whether it is
+// the better one for rank k, a workgroup's scratch and LDS for
 // a job of width w in a launch whose widest is wmax, the workgroups resident
 // at once, and the launches, one per kind of kernel the widths need (`share` of
 // the resident workgroups at most, as many as the scratch holds; kind k takes
@@ -102,6 +103,7 @@ constexpr int kStreamKinds = 5;
 constexpr int kStreamNarrow = 178;   // the widest of the narrow kinds, which share a launch: the built-in
                                      // strips are 992 windows to here, 1984 past it
 bool stream_takes(int32_t w, int32_t SBW);
+bool stream_ranks(int32_t w, int32_t k);
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);
 size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);
 int32_t stream_slots(int32_t w, int32_t SBW);

@@ -1340,6 +1340,23 @@ hipError_t profile_prepare(int32_t wmax) {
     return hipFuncSetAttribute(kernel_for(g), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
+// Whether the tiled kernel is the better one for rank k of a job of width w in
+// a launch of geometry g: both give the same bits there.
+static bool tiled_better(int32_t w, int32_t k, const Geo &g) {
+    return !stream_ranks(w, k) && geo_code(geo_heuristic(w)) == geo_code(g);
+}
+// Whether `tiles` of the tiled kernel fill enough of the `grid` workgroups of
+// geometry g: below three quarters of the resident ones (half, where one workgroup
+// has a CU) the streaming kernel's strips, eight or more to a tile, are the
+// better split at any rank.  Time of strips over tiles', 4 000 .. 40 000 points of
+// a regime series / a random walk, k = w, by the share of the resident workgroups:
+// w = 47: 0.5 1.1 / 0.7, 0.6 1.3 / 1.0, 1.3 1.3 / 1.0; w = 85: 0.3 1.0 / 0.6, 0.7
+// 1.0 / 0.8, 1.4 0.9 / 0.9; w = 265: 0.3 0.5 / 0.4, 0.4 0.7 / 0.8, 0.7 0.9 / 1.0.
+static bool tiles_fill(int64_t tiles, int32_t grid, const Geo &g) {
+    const int64_t slots = kCUs * (512 / g.NT);
+    return std::min<int64_t>(tiles, grid) * 4 >= (g.NT == 256 ? 3 : 2) * slots;
+}
+
 hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uint32_t *counter,
                                 hipStream_t st) {
     if (n < 1 || n > kMaxJobs || grid < 1) return hipErrorInvalidValue;
@@ -1349,8 +1366,12 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
     if (!geometry_ok(wmax, g)) return hipErrorInvalidValue;
     // The streaming kernel runs the jobs it takes where the launch has the
     // built-in geometry; explicitly chosen geometries and re-anchoring inside
-    // the rows run k_profile.
+    // the rows run k_profile, and so do the ranks that it is the better one for.
     const bool builtin = geo_code(g) == geo_code(geo_heuristic(wmax));
+    int64_t slow = 0;
+    for (int i = 0; i < n; ++i)
+        if (tiled_better(jobs[i].w, jobs[i].k, g)) slow += ((jobs[i].Nm + g.JT - 1) / g.JT) * (int64_t)jobs[i].nq;
+    const bool fill = tiles_fill(slow, grid, g);
     // Narrow jobs keep their own strips beside wider ones: in those of 1984
     // windows a workgroup has six waves, and at the narrow kinds' registers a
     // second one does not fit the CU's SIMDs (lengths 64 and 900 in one launch,
@@ -1367,7 +1388,8 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
     for (int i = 0; i < n; ++i) {
         const bool anchored = jobs[i].anchor_every > 0;
         const int set = jobs[i].w <= kStreamNarrow ? 0 : 1;
-        if (builtin && !anchored && stream_takes(jobs[i].w, gs[set].SBW)) {
+        if (builtin && !anchored && stream_takes(jobs[i].w, gs[set].SBW) &&
+            !(fill && tiled_better(jobs[i].w, jobs[i].k, g))) {
             strips[set][ns[set]++] = jobs[i];
             continue;
         }
@@ -1394,6 +1416,15 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
     const size_t lds = 4 * lds_floats(wmax, g);
     void *args[] = {&a};
     return hipLaunchKernel(kernel_for(g), dim3(grid), dim3(g.NT), args, lds, st);
+}
+
+// For the tests and the benchmark, not part of the ABI: whether the streaming
+// kernel runs nq queries of rank k against Nm windows in the built-in geometry.
+extern "C" int pst_host_streams(int32_t w, int32_t k, int64_t Nm, int64_t nq) {
+    if (w < 1 || w > kMaxW) return 0;
+    const Geo g = geo_heuristic(w);
+    const int64_t tiles = ((Nm + g.JT - 1) / g.JT) * nq;
+    return stream_takes(w, g.SBW) && !(tiles_fill(tiles, kCUs * (512 / g.NT), g) && tiled_better(w, k, g));
 }
 
 hipError_t launch_profile(const ProfileJob &job, uint32_t *counter, hipStream_t st) {

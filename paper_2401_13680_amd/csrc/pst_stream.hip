@@ -1372,15 +1372,40 @@ size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW) {
     return 4 * (size_t)Lds(H, w, Dims(stream_group(w), H, w, stream_threads(wmax, SBW), SBW)).total;
 }
 
-// k_profile keeps the windows that hold no two groups of six columns.  Above it
-// is never the better one (ms, l = m/2, k_profile against this kernel; 50 000
-// points of a regime series / a random walk): w = 12: 14.6 / 14.3 against 8.7 /
-// 8.6, w = 17: 16.2 / 16.0 against 7.7 / 7.7, w = 24: 14.0 / 13.8 against 5.5 /
-// 5.4, w = 33: 6.4 / 5.7 against 4.9 / 5.1, w = 65: 4.2 / 4.7 against 2.9 / 3.8;
-// 5 000 points: w = 12: 0.51 against 0.20, w = 33: 0.45 against 0.13.
+// k_profile keeps the windows that hold no two groups of six columns.  From
+// there to w = 552 this kernel is the better one at the default rank (ms, l =
+// m/2, k_profile against it; 50 000 points of a regime series / a random walk):
+// w = 12: 14.6 / 14.3 against 8.7 / 8.6, w = 17: 16.2 / 16.0 against 7.7 / 7.7,
+// w = 24: 14.0 / 13.8 against 5.5 / 5.4, w = 33: 6.4 / 5.7 against 4.9 / 5.1,
+// w = 65: 4.2 / 4.7 against 2.9 / 3.8; 5 000 points: w = 12: 0.51 against 0.20,
+// w = 33: 0.45 against 0.13.  w = 552 is where a block's rows and columns fill
+// kKindR = 18 keys a lane.
 bool stream_takes(int32_t w, int32_t SBW) {
     if (w < 12 || stream_kind(w) < 0) return false;
     return stream_threads(w, SBW) <= kMaxNT && stream_lds_bytes(w, w, SBW) + kLdsStatic <= kLdsCU;
+}
+
+// Ranks at which this kernel is the better one in a launch that fills the chip
+// either way.  Towards the middle of a window's 2w values the bounds leave most
+// rows open, the more so the wider a group is against w, while k_profile's time
+// hardly depends on k.  Time of this kernel over k_profile's, 50 000 and 60 000
+// points, the worse of a regime series and a random walk / white noise, on both
+// sides of each line: w = 17: k = 16 0.8 / 0.9, 17 1.4 / 1.5; w = 33: k = 10
+// 0.96 / 1.0, 13 1.02 / 1.2, 33 1.8 / 2.2; w = 47: k = 16 0.9 / 0.9, 19 1.3 / 1.4;
+// w = 65: k = 26 1.03 / 1.1, 49 1.14 / 1.4; w = 90: k = 54 0.95 / 1.2, 68 1.08 /
+// 1.4; w = 265: k = 133 0.98 / 1.3, 265 1.2 / 1.5.  The largest value (k = 2w) is
+// cheap again but at w = 265 .. 289 and 32 .. 35.  w = 24 .. 31: 0.3 .. 0.8 at
+// every rank (a walk's), 144 .. 264 and 290 on: 1.0 at the most, 1.3 in noise.
+bool stream_ranks(int32_t w, int32_t k) {
+    if (k >= 2 * w) return w < 32 || (w >= 36 && w < 265) || w >= 290;
+    if (w < 24) return k <= kMaxRank;
+    if (w < 32) return true;
+    if (w < 36) return k <= w / 3;
+    if (w < 48) return k <= kMaxRank;
+    if (w < 80) return 5 * k <= 2 * w;
+    if (w < 144) return 5 * k <= 3 * w;
+    if (w >= 265 && w < 290) return 2 * k <= w;
+    return true;
 }
 
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW) {

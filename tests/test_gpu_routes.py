@@ -1,0 +1,52 @@
+"""A profile set on both sides of the line between the two profile kernels, in
+launches that fill the chip: the same bits as the tiled kernel alone (reached
+through the re-anchor period of 2^20 rows, which anchors nowhere), also where
+jobs of both kernels share a batch."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_13680_amd import _lib, api, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def both(call):
+    ctx = api.context(0)
+    ctx.check(ctx.L.pst_set_option(ctx.h, _lib.PST_OPT_ANCHOR_EVERY, 1 << 20))
+    try:
+        ref = call(ctx)
+    finally:
+        ctx.check(ctx.L.pst_set_option(ctx.h, _lib.PST_OPT_ANCHOR_EVERY, 0))
+    return ref, call(ctx)
+
+
+def streams(w, k, Nm, nq):
+    return bool(_lib.load().pst_host_streams(ctypes.c_int32(w), ctypes.c_int32(k), ctypes.c_int64(Nm),
+                                             ctypes.c_int64(nq)))
+
+
+@pytest.mark.parametrize("w,line", [(17, 16), (33, 11), (47, 16), (65, 26), (129, 77), (265, 132)])
+def test_both_sides_of_the_line(w, line):
+    m, l = 2 * w - 1, w
+    n = 42_000 if w > 178 else 31_000
+    T = torch.from_numpy(synth.regime_series(n, w, synth.SHAPES6, len_range=(400, 2500)).x).cuda()
+    for k in (line, line + 1, 2 * w):
+        assert streams(w, k, n - m + 1, n // m) == (k == line or (k == 2 * w and w not in (33, 265))), (w, k)
+        (Dr, mr), (D, mx) = both(lambda c: api.profile_set(T, m, l, k, ctx=c))
+        assert torch.equal(D, Dr) and torch.equal(mx, mr), (w, k, int((D != Dr).sum()))
+
+
+def test_jobs_of_both_kernels_in_a_batch():
+    """Two lengths of one geometry, one on each side of the line: w = 33 at its
+    default rank of 13 (l = 3/4 m) and w = 64 at 13."""
+    ms, ls = [128, 127], [96, 64]
+    n = 60_000
+    assert not streams(33, 13, n - 127, n // 128) and streams(64, 13, n - 126, n // 127)
+    assert api.geometry(33) == api.geometry(64)
+    T = torch.from_numpy(synth.regime_series(n, 7, synth.SHAPES6, len_range=(400, 2500)).x).cuda()
+    ref, got = both(lambda c: api.select_length(T, ms, 3, l_list=ls, ctx=c))
+    assert got == ref
+    assert api.select_length(T, ms, 3, l_list=ls, batched=False) == got
