@@ -73,6 +73,7 @@ constexpr int kMaxNT = 448;          // threads of the widest strip
 constexpr int kSelect = 64 * 25;     // listed values that a wave holds in LDS
 constexpr int kSelectPad = 32 * 49;  // read past them, never used
 constexpr int kKeep = 32;            // keys of a long list that a lane keeps
+constexpr int kOpen = 64;            // open items of a block with one upper half that are looked at whole
 constexpr int kMaxRank = 16;         // smallest keys that a lane keeps of a block
 constexpr uint32_t kOne = 0x3F800000u;   // key of y = 1, the largest
 constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
@@ -729,9 +730,21 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
             }
             exact = ce >= k;
         }
-        if (!H && exact) {
+        // (an upper half of zero is y = 0 alone: y is a multiple of 2^-50)
+        if (exact && (!H || lo == 0u)) {
             if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
             continue;
+        }
+        if constexpr (H) {
+            if (exact) {
+                int open = 0;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) open += votes(C[r] >= lo && U[r] <= lo);
+                if (open > kOpen) {
+                    if (lane == 0) blk[a] = make_uint4(lo, 0u, 0u, kNone);   // for equal_blocks
+                    continue;
+                }
+            }
         }
         // below lo everywhere; listed: the rest that may be at most hi
         int below = 0, n = 0;
@@ -763,10 +776,93 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
     flush();
 }
 
+// The blocks of half keys that block_bounds left: one upper half holds the k-th
+// smallest U and C and more than kOpen items (repeats and constant stretches give
+// equal values).  Bounds and list from the whole minima gm of the rows in that
+// upper half; those below it count as 0, those above it not at all.  Mostly the
+// value is then known, where all those rows' pieces were kept and selected among
+// (30 000 points, 40 000 at w = 264, l = m/2, before -> now, k_profile; a quarter of
+// a regime series constant: w = 230: 3.0 -> 1.25, 2.4 ms, w = 264: 4.8 -> 2.6, 3.6;
+// period 40, with the blocks at y = 0 that block_bounds settles: w = 230: 4.4 ->
+// 0.54, 1.9, w = 264: 6.9 -> 1.3, 2.6; a walk of 200 000, w = 257: 43.1 -> 41.3).
+template <int G, int NR>
+__device__ __forceinline__ void equal_blocks(int a0, int a1, int w, int k, int CS, const Dims &d, const uint16_t *bm,
+                                             const uint32_t *gm, const uint32_t *colk, uint32_t *need, uint4 *blk,
+                                             uint2 *list, int lane) {
+    const int gc = w / G - 1, ge = 1 + (w - 2) / G - gc, rem = w % G;   // as in block_bounds
+    const int live = min((CS + WCOL - 1) / WCOL * (WCOL / G), d.NG);    // groups that the first pass wrote
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int a = a0; a < a1; ++a) {
+        // opaque, so that no row's address is kept in registers from block to block
+        // (89 spilled registers with them, 41 without)
+        asm volatile("" : "+v"(lane));
+        if (uni((int)blk[a].w) != (int)kNone) continue;
+        const uint32_t half = (uint32_t)uni((int)blk[a].x);
+        uint32_t U[NR], C[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int x = lane + 64 * r, cx = x - w, cg = a * G + cx;
+            U[r] = C[r] = kNone;
+            if (x < w) {
+                const uint16_t *hb = bm + x * d.ldg + a;
+                uint32_t c = kNone;
+                for (int q = 1; q <= gc; ++q) c = min(c, (uint32_t)hb[q]);
+                const uint32_t u = min(min(c, (uint32_t)hb[0]), min((uint32_t)hb[gc + 1], (uint32_t)hb[gc + ge]));
+                if (c < half) {
+                    U[r] = C[r] = 0u;
+                } else if (u <= half) {
+                    const uint32_t *row = gm + x * d.NG + a;
+                    c = kNone;
+                    for (int q = 1; q <= gc; ++q) c = min(c, row[q]);
+                    C[r] = c;
+                    U[r] = min(min(c, row[0]), min(row[min(gc + 1, live - 1 - a)], row[min(gc + ge, live - 1 - a)]));
+                }
+            } else if (cx < w + G - 1 && cg < CS && colk[cg] >> kHalfShift <= half) {
+                U[r] = colk[cg];
+                if (cx >= G - 1 && cx < w) C[r] = U[r];
+            }
+        }
+        const int under = (int)(half << kHalfShift) - 1, top = under + (1 << kHalfShift);
+        const uint32_t lo = find_rank<NR>(U, k, under, count_le<NR>(U, (uint32_t)under), top,
+                                          count_le<NR>(U, (uint32_t)top), -1);
+        const int cl = count_le<NR>(C, lo);
+        if (cl >= k) {
+            if (lane == 0) blk[a] = make_uint4(lo, lo, 0u, 0u);
+            continue;
+        }
+        const uint32_t hi = find_rank<NR>(C, k, (int)lo, cl, top, count_le<NR>(C, (uint32_t)top), -1);
+        int below = 0, n = 0;
+        uint2 *la = list + (size_t)a * d.items;
+        const int gr = a + w / G;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int x = lane + 64 * r;
+            const bool b = C[r] < lo, in = !b && U[r] <= hi;
+            below += votes(b);
+            const uint64_t m = __ballot(in);
+            if (in) {
+                const int pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (x < w) {
+                    uint32_t *nd = need + x * d.NGW;
+                    atomicOr(nd + (a >> 4), 1u << (a & 15));
+                    if (gr < d.NG) atomicOr(nd + (gr >> 4), 1u << (gr & 15));
+                    if (rem >= 2 && gr + 1 < d.NG) atomicOr(nd + ((gr + 1) >> 4), 1u << ((gr + 1) & 15));
+                }
+                la[pos] = x < w ? make_uint2((uint32_t)x, C[r]) : make_uint2(0x80000000u | (uint32_t)(x - w), U[r]);
+            }
+            n += __popcll(m);
+        }
+        if (lane == 0) blk[a] = make_uint4(lo, hi, (uint32_t)below, (uint32_t)n);
+    }
+}
+
 // block_bounds with the registers that w needs.
 template <int G, bool H, int KR>
 __device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int CS, const Dims &d, const uint32_t *bm,
-                                             const uint32_t *colk, uint32_t *need, uint4 *blk, uint2 *list, int lane) {
+                                             const uint32_t *gm, const uint32_t *colk, uint32_t *need, uint4 *blk,
+                                             uint2 *list, int lane) {
     const int nr = (d.items + 63) / 64;
 #define BOUNDS(NR, GC0, GC1) block_bounds<G, H, NR, GC0, GC1>(a0, a1, w, k, CS, d, bm, colk, need, blk, list, lane)
     // the widths of each kind: see stream_group and kKindR
@@ -782,6 +878,7 @@ __device__ __forceinline__ void strip_bounds(int a0, int a1, int w, int k, int C
     } else if constexpr (H) {
         if (nr <= 7) BOUNDS(7, 0, 0);
         else BOUNDS(9, 0, 0);
+        equal_blocks<G, KR>(a0, a1, w, k, CS, d, (const uint16_t *)bm, gm, colk, need, blk, list, lane);
     } else {
         if (nr <= 13) BOUNDS(13, 4, 7);
         else BOUNDS(18, 6, 10);
@@ -1034,15 +1131,16 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
             if constexpr (H) ((uint16_t *)bm)[i * d.ldg + g] = (uint16_t)(kOne >> kHalfShift);
             else bm[i * d.ldg + g] = kOne;
         }
-    lds_barrier();
+    if constexpr (H) __syncthreads();   // the exact group minima are read by other waves
+    else lds_barrier();
 
     float *pool = scr + X.pool;
     uint2 *list = (uint2 *)(scr + X.list);
     const int nblk = (S.JSe + G - 1) / G;
     const int per = (nblk + d.NW - 1) / d.NW;
     PROBE_MARK(t2);
-    strip_bounds<G, H, KR>(min(wv * per, nblk), min(wv * per + per, nblk), w, min(J.k, 2 * w), CS, d, bm, colk, need, blk,
-                    list, lane);
+    strip_bounds<G, H, KR>(min(wv * per, nblk), min(wv * per + per, nblk), w, min(J.k, 2 * w), CS, d, bm, gm, colk,
+                           need, blk, list, lane);
     PROBE_SPAN(2, t2);
     __syncthreads();
     PROBE_SPAN(3, t2);

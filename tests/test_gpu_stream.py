@@ -144,3 +144,25 @@ def test_runs_of_strips_in_a_batch():
     T = torch.from_numpy(series(40000, 44)).cuda()
     ref, got = both(lambda c: api.select_length(T, [64, 128], 3, ctx=c))
     assert ref == got
+
+
+@pytest.mark.parametrize("w", [179, 190, 200, 230, 264])
+@pytest.mark.parametrize("kind", ["period", "sine", "flat"])
+@pytest.mark.parametrize("short", [False, True])
+def test_equal_values_under_half_keys(w, kind, short):
+    """Blocks whose open rows share one upper half: exact repeats (mostly y = 0,
+    which an upper half of 0 settles) and constant stretches (y = 1/4), down to
+    a last strip of one window whose groups end inside the first wave."""
+    l = w // 3 if short else w - 1
+    m = w + l - 1
+    for windows in (1985, 2 * 1984 + 700):
+        n = max(windows + m - 1, 2 * m)
+        if kind == "period":
+            x = np.tile(np.random.default_rng(w).normal(size=40), n // 40 + 1)[:n]
+        elif kind == "sine":
+            x = np.sin(np.arange(n) * 2 * np.pi / 100.0)
+        else:
+            x = series(n, 51)
+            x[n // 4:n // 2] = 1.0
+        for k in (0, 1, w // 3, w, 2 * w):
+            same_set(x, m, l, k)
