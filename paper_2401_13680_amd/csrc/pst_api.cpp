@@ -655,17 +655,17 @@ int sweep_jobs(const SweepPlan &P, char *ws, int32_t grid, ProfileJob *jobs, int
 }
 
 // The profile launches of a sweep: one persistent launch per workgroup
-// shape among the lengths, widest first, each grid scaled like the widest
-// shape's (grid of P.grid).
-hipError_t launch_sweep_profiles(const SweepPlan &P, char *ws, int32_t grid, bool dynamic, hipStream_t st,
-                                 int32_t anchor, bool one_launch = false) {
+// shape among the lengths, widest first, each grid (and limit on the workgroups,
+// where one is set) scaled like the widest shape's (grid of P.grid).
+hipError_t launch_sweep_profiles(const SweepPlan &P, char *ws, int32_t grid, int32_t limit, bool dynamic,
+                                 hipStream_t st, int32_t anchor, bool one_launch = false) {
     ProfileJob jobs[kMaxJobs];
     const int nj = sweep_jobs(P, ws, grid, jobs, anchor);
     uint32_t *counter = (uint32_t *)(ws + P.o_counter);
     hipError_t e;
     if (one_launch) {  // every length in the widest one's geometry
         if ((e = launch_fill_u32(counter, kCounters, 0u, st)) != hipSuccess) return e;
-        return launch_profile_batch(jobs, nj, grid, dynamic ? counter : nullptr, st);
+        return launch_profile_batch(jobs, nj, grid, dynamic ? counter : nullptr, st, limit);
     }
     int done = 0;
     for (int32_t wg : P.shape_w) {
@@ -674,23 +674,28 @@ hipError_t launch_sweep_profiles(const SweepPlan &P, char *ws, int32_t grid, boo
         int cnt = 0;
         while (done + cnt < nj && profile_shape(jobs[done + cnt].w) == shape) ++cnt;
         if (cnt == 0) continue;
-        const int32_t g = std::max<int32_t>(1, (int32_t)((int64_t)profile_slots(wg) * grid / P.grid));
+        auto scaled = [&](int32_t v) {
+            return std::max<int32_t>(1, (int32_t)((int64_t)profile_slots(wg) * v / P.grid));
+        };
+        const int32_t g = scaled(grid);
         for (int j = done; j < done + cnt; ++j) jobs[j].grid = g;
         if ((e = launch_fill_u32(counter, kCounters, 0u, st)) != hipSuccess) return e;
-        if ((e = launch_profile_batch(jobs + done, cnt, g, dynamic ? counter : nullptr, st)) != hipSuccess) return e;
+        if ((e = launch_profile_batch(jobs + done, cnt, g, dynamic ? counter : nullptr, st,
+                                      limit > 0 ? scaled(limit) : 0)) != hipSuccess)
+            return e;
         done += cnt;
     }
     return hipSuccess;
 }
 
-hipError_t enqueue_sweep(const SweepPlan &P, const double *T, char *ws, int32_t grid, bool dynamic,
+hipError_t enqueue_sweep(const SweepPlan &P, const double *T, char *ws, int32_t grid, int32_t limit, bool dynamic,
                          hipStream_t st, int32_t anchor, bool one_launch) {
     hipError_t e;
     for (size_t j = 0; j < P.ls.size(); ++j)
         if ((e = launch_series_stats(T, ws + P.o_stats[j], P.SL[j], st)) != hipSuccess) return e;
     for (int i = 0; i < P.nm; ++i)
         if ((e = launch_fill_u32((uint32_t *)(ws + P.gb[i].dmax), 1, 0u, st)) != hipSuccess) return e;
-    if ((e = launch_sweep_profiles(P, ws, grid, dynamic, st, anchor, one_launch)) != hipSuccess) return e;
+    if ((e = launch_sweep_profiles(P, ws, grid, limit, dynamic, st, anchor, one_launch)) != hipSuccess) return e;
     SweepGather Gt{};
     Gt.nm = P.nm;
     Gt.K = P.K;
@@ -873,7 +878,7 @@ int autotune(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, TuneVal 
     for (int32_t wg : P.shape_w) HIPCHK(c, profile_prepare(wg));
     for (const auto &cf : cand) {
         HIPCHK(c, hipEventRecord(a, c->stream));
-        HIPCHK(c, launch_sweep_profiles(P, ws, cf[0], cf[1] != 0, c->stream, 0));
+        HIPCHK(c, launch_sweep_profiles(P, ws, cf[0], 0, cf[1] != 0, c->stream, 0));
         HIPCHK(c, hipEventRecord(b, c->stream));
         HIPCHK(c, hipEventSynchronize(b));
         float ms = 0.0f;
@@ -898,16 +903,19 @@ int autotune(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, TuneVal 
 int run_sweep(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, size_t ws_bytes,
               const int32_t *m_list, const int32_t *l_list, std::vector<double> *res) {
     TuneVal cfg{c->opt_grid > 0 ? std::min(c->opt_grid, P.grid) : P.grid, c->opt_dynamic, 0.0f};
-    if (c->opt_autotune) {
+    int32_t limit = c->opt_grid;
+    if (c->opt_autotune) {  // (the tuned grid in place of the option's)
         const int rc = autotune(c, P, T, ws, &cfg);
         if (rc) return rc;
+        limit = 0;
     }
     for (int32_t wg : P.shape_w) HIPCHK(c, profile_prepare(wg));
     if (!c->opt_graph) {
-        HIPCHK(c, enqueue_sweep(P, T, ws, cfg.grid, cfg.dynamic != 0, c->stream, c->opt_anchor, c->opt_one_launch));
+        HIPCHK(c, enqueue_sweep(P, T, ws, cfg.grid, limit, cfg.dynamic != 0, c->stream, c->opt_anchor,
+                                c->opt_one_launch));
     } else {
         std::vector<int64_t> key = {(int64_t)(uintptr_t)T, P.L[0].n, (int64_t)(uintptr_t)ws,
-                                    (int64_t)ws_bytes, P.nm, P.K, cfg.grid, cfg.dynamic, c->opt_anchor,
+                                    (int64_t)ws_bytes, P.nm, P.K, cfg.grid, limit, cfg.dynamic, c->opt_anchor,
                                     c->opt_one_launch};
         for (int i = 0; i < P.nm; ++i) {
             key.push_back(m_list[i]);
@@ -921,7 +929,7 @@ int run_sweep(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, size_t 
             if (!c->cap) HIPCHK(c, hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
             HIPCHK(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
             const hipError_t eq =
-                enqueue_sweep(P, T, ws, cfg.grid, cfg.dynamic != 0, c->cap, c->opt_anchor, c->opt_one_launch);
+                enqueue_sweep(P, T, ws, cfg.grid, limit, cfg.dynamic != 0, c->cap, c->opt_anchor, c->opt_one_launch);
             hipGraph_t graph = nullptr;
             const hipError_t ee = hipStreamEndCapture(c->cap, &graph);
             HIPCHK(c, eq);

@@ -70,8 +70,9 @@ struct ProfileBatch {
 };
 int64_t profile_tiles(const ProfileJob &j);
 hipError_t profile_prepare(int32_t wmax);  // kernel attributes; call outside graph capture
+// limit > 0: the most workgroups of any of the launches (with grid at most that).
 hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uint32_t *counter,
-                                hipStream_t st);
+                                hipStream_t st, int32_t limit = 0);
 int32_t profile_tile_windows(int32_t w);  // windows per tile
 int32_t profile_slots(int32_t w);                 // profile workgroups resident at once
 int32_t profile_shape(int32_t w);                 // equal for w that get the same workgroup shape
@@ -97,8 +98,9 @@ size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true
 // the better one for rank k, a workgroup's scratch and LDS for
 // a job of width w in a launch whose widest is wmax, the workgroups resident
 // at once, and the launches, one per kind of kernel the widths need (`share` of
-// the resident workgroups at most, as many as the scratch holds; kind k takes
-// counter[k], zeroed beforehand, when counter is set).
+// the resident workgroups at most, `limit` of them where it is set, as many as
+// the scratch holds; kind k takes counter[k], zeroed beforehand, when counter is
+// set).
 constexpr int kStreamKinds = 5;
 constexpr int kStreamNarrow = 178;   // the widest of the narrow kinds, which share a launch: the built-in
                                      // strips are 992 windows to here, 1984 past it
@@ -109,7 +111,7 @@ size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);
 int32_t stream_slots(int32_t w, int32_t SBW);
 hipError_t stream_prepare();
 hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
-                         double share, uint32_t *counter, hipStream_t st);
+                         double share, int32_t limit, uint32_t *counter, hipStream_t st);
 
 // Greedy snippet search and its by-products, all on device (eqs. 6-8, 16-18).
 struct GreedyJob {

@@ -1358,7 +1358,7 @@ static bool tiles_fill(int64_t tiles, int32_t grid, const Geo &g) {
 }
 
 hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uint32_t *counter,
-                                hipStream_t st) {
+                                hipStream_t st, int32_t limit) {
     if (n < 1 || n > kMaxJobs || grid < 1) return hipErrorInvalidValue;
     int wmax = 0;
     for (int i = 0; i < n; ++i) wmax = jobs[i].w > wmax ? jobs[i].w : wmax;
@@ -1408,7 +1408,7 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
         for (int set = 1; set >= 0; --set) {
             if (ns[set] == 0) continue;
             const hipError_t e = launch_stream(strips[set], ns[set], gs[set].SBW, gs[set].JT / gs[set].SBW, room, share,
-                                               counter, st);
+                                               limit, counter, st);
             if (e != hipSuccess) return e;
         }
         if (a.B.njobs == 0) return hipSuccess;

@@ -1530,7 +1530,7 @@ hipError_t stream_prepare() {
 }
 
 hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
-                         double share, uint32_t *counter, hipStream_t st) {
+                         double share, int32_t limit, uint32_t *counter, hipStream_t st) {
     if (n < 1 || n > kMaxJobs) return hipErrorInvalidValue;
     int kinds = 0;
     for (int i = 0; i < n; ++i) {
@@ -1568,7 +1568,8 @@ hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t til
                 lds = std::max(lds, stream_lds_bytes(jobs[i].w, wmax, SBW));
             }
         if (lds + kLdsStatic > kLdsCU) return hipErrorInvalidValue;
-        const int64_t most = std::max<int64_t>(1, (int64_t)(share * stream_slots(wmax, SBW)));
+        const int32_t slots = stream_slots(wmax, SBW);
+        const int64_t most = limit > 0 ? std::min(limit, slots) : std::max<int64_t>(1, (int64_t)(share * slots));
         a.tile = tile;
         a.run = tile;
         while (a.run > 1 && (a.run % 2 != 0 || strips < kRunsPerSlot * most * a.run)) a.run = a.run % 2 ? 1 : a.run / 2;
