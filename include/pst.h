@@ -365,8 +365,9 @@ int pst_label_f1(pst_ctx *ctx, const int32_t *owner_dev, int64_t n, int32_t m, i
  *                          sweep's profile launch on first use of a shape
  *                          bucket [0, 1]; the choice is kept per process and,
  *                          if the environment variable PST_AUTOTUNE_CACHE names
- *                          a file, appended there and read back later (a grid
- *                          read back never exceeds the workspace's slots)
+ *                          a file, appended there and read back later by the
+ *                          build that timed it (a grid read back never exceeds
+ *                          the workspace's slots)
  *   PST_OPT_PROFILE_GRID   persistent workgroups of the sweep launch [0 = all
  *                          that are resident at once]
  *   PST_OPT_DYNAMIC_TILES  hand tiles out from a device counter [1, 0]
@@ -417,8 +418,8 @@ int pst_set_option(pst_ctx *ctx, int option, int64_t value);
  * pst_workspace_bytes(n, m, l, 1)),
  * installs the fastest and returns its code and launch time; the choice is
  * remembered per (GPU architecture, w) in the process and, if
- * PST_AUTOTUNE_CACHE names a file, there ("geo arch w code ms" lines), and
- * reused without timing. */
+ * PST_AUTOTUNE_CACHE names a file, there ("geo arch w code ms build" lines), and
+ * reused by the same build without timing. */
 int pst_geometry_candidates(int32_t w, int32_t *codes, int32_t max);
 int32_t pst_geometry(int32_t w);
 int pst_set_geometry(int32_t w, int32_t code);

@@ -25,6 +25,19 @@ HIPCC_FLAGS = [
 ]
 
 
+def build_id() -> str:
+    """sha256 (its first 16 digits) of the library's sources and compiler flags.
+    Lines of the autotuner's cache file carry it: a choice that another build
+    timed is not taken."""
+    import hashlib
+    h = hashlib.sha256(" ".join(HIPCC_FLAGS).encode())
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".cpp", ".h", ".inc")):
+            with open(os.path.join(CSRC, name), "rb") as f:
+                h.update(name.encode() + b"\0" + f.read())
+    return h.hexdigest()[:16]
+
+
 def build_library(verbose: bool = False, probe: bool = False) -> str:
     """Build libpst.so; probe=True builds libpst_probe.so instead, whose
     profile kernel counts how often each selection phase runs (pst_probe_read)."""
@@ -36,7 +49,8 @@ def build_library(verbose: bool = False, probe: bool = False) -> str:
         obj = os.path.join(CSRC, "_obj_" + os.path.splitext(src)[0] + tag + ".o")
         cmd = [hipcc, *HIPCC_FLAGS, *(["-DPST_PROBE"] if probe else []), "-c", os.path.join(CSRC, src), "-o", obj]
         if src.endswith(".cpp"):
-            cmd = [hipcc, "-O3", "-std=c++17", "-fPIC", "-c", os.path.join(CSRC, src), "-o", obj]
+            cmd = [hipcc, "-O3", "-std=c++17", "-fPIC", f'-DPST_BUILD_ID="{build_id()}"', "-c",
+                   os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)

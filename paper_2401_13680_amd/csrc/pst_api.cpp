@@ -721,8 +721,14 @@ hipError_t enqueue_sweep(const SweepPlan &P, const double *T, char *ws, int32_t 
 // ---- autotuner: persistent grid size and tile scheduling of the batched
 // profile launch, timed on the caller's own problem the first time a shape
 // bucket is seen; remembered per process and optionally in a text file named
-// by PST_AUTOTUNE_CACHE ("arch wmax tiles_log2 grid dynamic ms" per line).
-// The choice only moves tiles between workgroups: results are identical.
+// by PST_AUTOTUNE_CACHE ("arch wmax tiles_log2 grid dynamic ms build" per line).
+// The choice only moves tiles between workgroups: results are identical.  A
+// line counts only in the build that timed it: an earlier build's choice is of
+// other kernels (a geometry of the tiled kernel once tuned would keep its w
+// from the streaming kernel that came after).
+#ifndef PST_BUILD_ID
+#error "PST_BUILD_ID: the hash of the sources, set by build.py"
+#endif
 using TuneKey = std::tuple<std::string, int, int>;
 struct TuneVal {
     int grid, dynamic;
@@ -744,13 +750,14 @@ void tune_load_locked() {
     if (!f) return;
     char line[256];
     while (std::fgets(line, sizeof line, f)) {
-        char arch[64];
+        char arch[64], build[64];
         int wm, tl, gr, dy, code;
         float ms;
-        if (std::sscanf(line, "geo %63s %d %d %f", arch, &wm, &code, &ms) == 4)
-            g_geo_tuned[{arch, wm}] = {code, ms};
-        else if (std::sscanf(line, "%63s %d %d %d %d %f", arch, &wm, &tl, &gr, &dy, &ms) == 6)
-            g_tuned[TuneKey(arch, wm, tl)] = TuneVal{gr, dy, ms};
+        if (std::sscanf(line, "geo %63s %d %d %f %63s", arch, &wm, &code, &ms, build) == 5) {
+            if (std::strcmp(build, PST_BUILD_ID) == 0) g_geo_tuned[{arch, wm}] = {code, ms};
+        } else if (std::sscanf(line, "%63s %d %d %d %d %f %63s", arch, &wm, &tl, &gr, &dy, &ms, build) == 7) {
+            if (std::strcmp(build, PST_BUILD_ID) == 0) g_tuned[TuneKey(arch, wm, tl)] = TuneVal{gr, dy, ms};
+        }
     }
     std::fclose(f);
 }
@@ -829,7 +836,7 @@ int tune_geometry_job(pst_ctx *c, ProfileJob J, int32_t *code_out, float *ms_out
     g_geo_tuned[{arch, w}] = {best, best_ms};
     if (const char *path = std::getenv("PST_AUTOTUNE_CACHE")) {
         if (FILE *f = std::fopen(path, "a")) {
-            std::fprintf(f, "geo %s %d %d %.4f\n", arch.c_str(), w, best, best_ms);
+            std::fprintf(f, "geo %s %d %d %.4f %s\n", arch.c_str(), w, best, best_ms, PST_BUILD_ID);
             std::fclose(f);
         }
     }
@@ -856,8 +863,8 @@ int autotune(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, TuneVal 
         tune_load_locked();
         auto it = g_tuned.find(key);
         if (it != g_tuned.end()) {
-            // a line of the cache file may come from another build: never more
-            // workgroups than the workspace has scratch slots for
+            // whatever a line of the cache file says: never more workgroups than
+            // the workspace has scratch slots for
             *out = it->second;
             out->grid = std::max(1, std::min(out->grid, P.grid));
             out->dynamic = out->dynamic != 0;
@@ -891,8 +898,8 @@ int autotune(pst_ctx *c, const SweepPlan &P, const double *T, char *ws, TuneVal 
     g_tuned[key] = best;
     if (const char *path = std::getenv("PST_AUTOTUNE_CACHE")) {
         if (FILE *f = std::fopen(path, "a")) {
-            std::fprintf(f, "%s %d %d %d %d %.4f\n", std::get<0>(key).c_str(), P.wmax, tl, best.grid,
-                         best.dynamic, best.ms);
+            std::fprintf(f, "%s %d %d %d %d %.4f %s\n", std::get<0>(key).c_str(), P.wmax, tl, best.grid,
+                         best.dynamic, best.ms, PST_BUILD_ID);
             std::fclose(f);
         }
     }
