@@ -109,6 +109,7 @@ bool stream_ranks(int32_t w, int32_t k);
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);
 size_t stream_lds_bytes(int32_t w, int32_t wmax, int32_t SBW);
 int32_t stream_slots(int32_t w, int32_t SBW);
+hipError_t stream_occupancy(int32_t w, int32_t SBW, int *per_cu);
 hipError_t stream_prepare();
 hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t tile, size_t scratch_floats,
                          double share, int32_t limit, uint32_t *counter, hipStream_t st);

@@ -1427,6 +1427,18 @@ extern "C" int pst_host_streams(int32_t w, int32_t k, int64_t Nm, int64_t nq) {
     return stream_takes(w, g.SBW) && !(tiles_fill(tiles, kCUs * (512 / g.NT), g) && tiled_better(w, k, g));
 }
 
+// For the tests: streaming workgroups of w resident at once, as the launches
+// plan them and (on a device) by the runtime; -1 where it does not run w.
+extern "C" int pst_host_stream_resident(int32_t w) {
+    const int32_t SBW = w >= 1 && w <= kMaxW ? geo_heuristic(w).SBW : 0;
+    return SBW && stream_takes(w, SBW) ? stream_slots(w, SBW) : -1;
+}
+extern "C" int pst_device_stream_resident(int32_t w) {
+    int per_cu = 0;
+    if (pst_host_stream_resident(w) < 0 || stream_occupancy(w, geo_heuristic(w).SBW, &per_cu) != hipSuccess) return -1;
+    return kCUs * per_cu;
+}
+
 hipError_t launch_profile(const ProfileJob &job, uint32_t *counter, hipStream_t st) {
     hipError_t e = profile_prepare(job.w);
     if (e != hipSuccess) return e;

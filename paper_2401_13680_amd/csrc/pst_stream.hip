@@ -1455,7 +1455,8 @@ const void *const kKernels[kStreamKinds + 1] = {
 constexpr int64_t kRunsPerSlot = 3;
 constexpr int64_t kTailStrips = 4;
 constexpr size_t kLdsCU = 160 * 1024;
-constexpr size_t kLdsStatic = 512;   // next_run, the vote of __syncthreads_or, alignment
+constexpr size_t kLdsStatic = 272;   // next_run and the vote of __syncthreads_or, as compiled
+constexpr size_t kLdsUnit = 1280;    // a workgroup's LDS is allocated in these
 
 int stream_threads(int w, int SBW) {
     const int by_col = (SBW + w - 1 + V - 1) / V;
@@ -1512,12 +1513,24 @@ size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW) {
     return Scratch(G, H, w, Dims(G, H, w, stream_threads(wmax, SBW), SBW)).total;
 }
 
-// Workgroups resident at once: LDS and the registers' waves.
+// Workgroups resident at once: LDS and the registers' waves, as the runtime counts
+// them at every w.  (With 512 bytes for the static LDS the plan left w = 264 one
+// workgroup a CU of two and w = 144 three of four: 60 000 points, l = w - 1, 4.9 ->
+// 3.0 and 2.8 -> 2.3 ms.)
 int32_t stream_slots(int32_t w, int32_t SBW) {
     const int NT = stream_threads(w, SBW);
-    const size_t by_lds = kLdsCU / (stream_lds_bytes(w, w, SBW) + kLdsStatic);
+    const size_t units = (stream_lds_bytes(w, w, SBW) + kLdsStatic + kLdsUnit - 1) / kLdsUnit;
+    const size_t by_lds = kLdsCU / (kLdsUnit * units);
     const size_t by_waves = 4 * kKindW[stream_kind(w)] / (NT / 64);
     return 256 * (int32_t)std::max<size_t>(1, std::min(by_lds, by_waves));
+}
+
+// Workgroups of the kernel of w resident on a CU, by the runtime.
+hipError_t stream_occupancy(int32_t w, int32_t SBW, int *per_cu) {
+    const hipError_t e = stream_prepare();
+    if (e != hipSuccess) return e;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kKernels[stream_kind(w)], stream_threads(w, SBW),
+                                                        stream_lds_bytes(w, w, SBW));
 }
 
 hipError_t stream_prepare() {

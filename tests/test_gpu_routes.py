@@ -50,3 +50,12 @@ def test_jobs_of_both_kernels_in_a_batch():
     ref, got = both(lambda c: api.select_length(T, ms, 3, l_list=ls, ctx=c))
     assert got == ref
     assert api.select_length(T, ms, 3, l_list=ls, batched=False) == got
+
+
+def test_resident_workgroups_are_the_runtimes():
+    """What the launches plan for against the runtime's count, at every width."""
+    L = _lib.load()
+    torch.cuda.init()
+    plan = {w: L.pst_host_stream_resident(ctypes.c_int32(w)) for w in range(12, 553)}
+    got = {w: L.pst_device_stream_resident(ctypes.c_int32(w)) for w in plan}
+    assert got == plan, {w: (plan[w], got[w]) for w in plan if got[w] != plan[w]}

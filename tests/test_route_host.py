@@ -37,3 +37,11 @@ def test_default_ranks_stream():
     assert all(streams(m - m // 2 + 1, (m + 9) // 10) for m in range(24, 1103))
     assert not any(streams(w, 1) for w in (1, 11, 553, 1025))
     assert [w for w in range(12, 553) if not streams(w, 2 * w)] == list(range(32, 36)) + list(range(265, 290))
+
+
+def test_resident_workgroups():
+    """Four a CU to w = 144, three to 178, two to 264, then one (the widest strips fill a CU's LDS)."""
+    got = {w: L.pst_host_stream_resident(ctypes.c_int32(w)) for w in range(12, 553)}
+    want = {w: 1024 if w <= 144 else 768 if w <= 178 else 512 if w <= 264 else 256 for w in got}
+    assert got == want, {w: (got[w], want[w]) for w in got if got[w] != want[w]}
+    assert L.pst_host_stream_resident(ctypes.c_int32(553)) == -1
