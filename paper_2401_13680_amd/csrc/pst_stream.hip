@@ -1321,7 +1321,9 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
                 PROBE_SPAN(11, t6);
                 continue;
             }
-            const int nr = (n0 + 63) / 64, nrr = nr <= 2 ? 2 : (nr <= KR / 2 ? KR / 2 : KR), stride = 64 * nrr;
+            // (half the kind's keys are fewer than two of each lane at KR = 3)
+            constexpr int KH = KR / 2 > 2 ? KR / 2 : 2;
+            const int nr = (n0 + 63) / 64, nrr = nr <= 2 ? 2 : (nr <= KH ? KH : KR), stride = 64 * nrr;
             uint32_t *vals = (uint32_t *)(scr + X.vals) + (size_t)wv * d.cap * G;
             for (int e = lane; e < stride; e += 64) {
                 uint32_t o[G];
@@ -1336,7 +1338,7 @@ __device__ __forceinline__ void run_strip(const Strip &S, float *sm, float *scr,
             const uint32_t lo = (uint32_t)uni((int)bl.x), hi = (uint32_t)uni((int)bl.y);
             uint32_t v = lo, res;
             if (nrr == 2) res = select_windows<2>(vals, np, n0, kk, v, lo, hi, lane);
-            else if (nrr == KR / 2) res = select_windows<KR / 2>(vals, np, n0, kk, v, lo, hi, lane);
+            else if (nrr == KH) res = select_windows<KH>(vals, np, n0, kk, v, lo, hi, lane);
             else res = select_windows<KR>(vals, np, n0, kk, v, lo, hi, lane);
             put(a, lane, lane < np, res);
             // the values are read before the next block's are written
@@ -1394,13 +1396,17 @@ constexpr bool kKindH[kStreamKinds] = {false, false, false, true, false};
 constexpr int kKindR[kStreamKinds] = {1, 3, 6, 9, 18};
 constexpr int kKindW[kStreamKinds] = {3, 3, 3, 4, 2};
 constexpr int kNarrow = 3;   // the first kinds, alike in what a CU holds of them
-__host__ __device__ inline int stream_kind(int w) {
-    constexpr int g[kStreamKinds] = {6, 12, 24, 24, 48}, r[kStreamKinds] = {1, 3, 6, 9, 18};
-    constexpr bool h[kStreamKinds] = {false, false, false, true, false};
-    for (int k = 0; k < kStreamKinds; ++k)
-        if (g[k] == stream_group(w) && h[k] == stream_half(w) && 2 * w + g[k] - 1 <= 64 * r[k]) return k;
-    return -1;
+template <int K>
+__host__ __device__ inline int stream_kind_from(int w) {
+    if constexpr (K == kStreamKinds) {
+        return -1;
+    } else {
+        constexpr int g = kKindG[K], r = kKindR[K];
+        constexpr bool h = kKindH[K];
+        return g == stream_group(w) && h == stream_half(w) && 2 * w + g - 1 <= 64 * r ? K : stream_kind_from<K + 1>(w);
+    }
 }
+__host__ __device__ inline int stream_kind(int w) { return stream_kind_from<0>(w); }
 
 // Jobs of the kinds K0 .. K1; NT and LDS are sized for the widest of the launch.
 template <int K0, int K1, int WPE>
@@ -1620,8 +1626,8 @@ hipError_t launch_stream(const ProfileJob *jobs, int n, int32_t SBW, int32_t til
 #ifdef PST_PROBE
 // Sums since the last reset: wave cycles of 0 setup and anchors, 1 the first
 // pass, 2 bounds, 3 bounds and their barrier, 4 the second pass, 5 selection,
-// 6 the listed rows' minima in it, 11 counted selections in it; 7 threshold
-// counts, 8 blocks, 9 listed items, 10 counted selections, 12 their steps.
+// 6 the listed rows' minima in it, 11 selections of long lists in it; 8 blocks,
+// 9 listed items, 10 blocks with long lists.
 extern "C" int pst_stream_probe_read(unsigned long long *out, int reset) {
     static unsigned long long buf[16 * 64];
     if (hipMemcpyFromSymbol(buf, HIP_SYMBOL(g_stream_probe), sizeof(buf)) != hipSuccess) return -3;
