@@ -59,3 +59,51 @@ def test_resident_workgroups_are_the_runtimes():
     plan = {w: L.pst_host_stream_resident(ctypes.c_int32(w)) for w in range(12, 553)}
     got = {w: L.pst_device_stream_resident(ctypes.c_int32(w)) for w in plan}
     assert got == plan, {w: (plan[w], got[w]) for w in plan if got[w] != plan[w]}
+
+
+def scores(T, ws, ctx=None, **kw):
+    """Scores of the lengths whose windows hold w = l + 1 subsequences."""
+    ms, ls = [2 * w - 2 for w in ws], [w - 1 for w in ws]
+    return api.select_length(T, ms, 3, l_list=ls, ctx=ctx, **kw)["scores"]
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("ws", [[9, 51], [9, 51, 201, 301, 531, 601], [531, 601], [9, 11]])
+def test_widths_of_both_kernels_in_one_launch(ws, graph):
+    """w = 9 and 601 are the tiled kernel's, the others stream; past w = 513 the
+    strips and tiles of every width are those of a launch of its own, so all scores
+    are the tiled kernel's, bit for bit.  Twice, with other work between."""
+    T = torch.from_numpy(synth.regime_series(6000, 45, synth.SHAPES6, len_range=(400, 2500)).x).cuda()
+    ref, got = both(lambda c: scores(T, ws, ctx=c, one_launch=True, graph=graph))
+    assert got == ref
+    alone = scores(T, ws, batched=False)
+    assert scores(T, ws, one_launch=True, graph=graph) == got
+    split = scores(T, ws, graph=graph)
+    assert split == alone and scores(T, ws, graph=graph) == alone
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_widths_of_both_kernels_beside_wide_strips(graph):
+    """Beside w = 301 (strips of 1984) the streaming widths up to 178 keep their own
+    strips and so their own bits; w = 9 runs in the tiles of w = 301."""
+    ws = [9, 51, 201, 301]
+    T = torch.from_numpy(synth.regime_series(6000, 46, synth.SHAPES6, len_range=(400, 2500)).x).cuda()
+    got = scores(T, ws, one_launch=True, graph=graph)
+    alone = scores(T, ws, batched=False)
+    assert got[1:] == alone[1:]
+    assert abs(got[0] - alone[0]) <= 1e-4 * max(1.0, abs(alone[0]))
+    assert scores(T, ws, one_launch=True, graph=graph) == got
+
+
+def test_server_batches_of_both_kernels():
+    """Requests of one shape that need both kernels, submitted together."""
+    specs = [(16, 8), (100, 50), (40, 20), (1060, 530), (1200, 600), (16, 8), (128, 96)]
+    xs = [torch.from_numpy(synth.regime_series(6000 + 500 * i, 47 + i, synth.SHAPES6, len_range=(400, 2500)).x).cuda()
+          for i in range(len(specs))]
+    srv = api.Server(0)
+    tickets = [srv.submit(x, m, l, 3) for x, (m, l) in zip(xs, specs)]
+    srv.drain()
+    got = [srv.poll(t) for t in tickets]
+    srv.close()
+    for g, x, (m, l) in zip(got, xs, specs):
+        assert g["status"] == 0 and g["records"] == api.snippets(x, m, l, 3)["records"], (m, l)
