@@ -166,3 +166,34 @@ def test_equal_values_under_half_keys(w, kind, short):
             x[n // 4:n // 2] = 1.0
         for k in (0, 1, w // 3, w, 2 * w):
             same_set(x, m, l, k)
+
+
+@pytest.mark.parametrize("w", [178, 179, 513, 514, 552, 553])
+@pytest.mark.parametrize("l", [7, 150])
+def test_widths_at_the_lines_of_the_dispatch(w, l):
+    """Strips of 992 windows to w = 178 and from 514, of 1984 between; the tiled kernel from 553."""
+    m = w + l - 1
+    same_set(series(4 * m + 2500, w), m, l)
+
+
+@pytest.mark.parametrize("w", [178, 514])
+@pytest.mark.parametrize("extra", [-1, 0, 1, 13])
+@pytest.mark.parametrize("strips", [1, 2, 9])
+def test_ragged_strips_of_992(w, extra, strips):
+    l = 64
+    m = w + l - 1
+    T = torch.from_numpy(series(strips * 992 + extra + m - 1, 11)).cuda()
+    Q = torch.from_numpy(series(m, 12)).cuda()
+    ref, got = both(lambda c: api.mpdist_profile(T, Q, l, ctx=c))
+    assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("k", [1, 31, 33, 178, 2 * 178 - 33, 2 * 178 - 31, 2 * 178])
+def test_long_lists_at_the_widest_kept(k):
+    """w = 178, the widest whose long lists keep the keys of two lanes a window."""
+    w = 178
+    rng = np.random.default_rng(w + k)
+    m = 2 * w - 2
+    n = 3 * m + 1400
+    same_set(np.cumsum(rng.normal(size=n)), m, w - 1, k)
+    same_set(rng.normal(size=n), m, w - 1, k)
