@@ -40,7 +40,7 @@ OPS_PER_CELL = 8
 PEAK_LANE_OPS = 256 * 64 * 2.4e9
 
 
-TRAFFIC_NOTE = os.path.join(ROOT, "profiles", "k_profile_traffic.md")
+TRAFFIC_NOTE = os.path.join(ROOT, "profiles", "profile_kernels_traffic.md")
 KERNEL_HASH = os.path.join(ROOT, "paper_2401_13680_amd", "libpst.k_profile.sha256")
 
 
@@ -52,8 +52,8 @@ def progress(msg):
 def measured_traffic(cells_per_launch, field="hbm bytes per cell"):
     """HBM bytes per profile launch: the committed FETCH_SIZE + WRITE_SIZE
     measurement (bytes per distance-matrix cell, copy-calibrated) times the
-    launch's cells, or None once the profile kernel's machine code differs from
-    the one measured (hash written by the build)."""
+    launch's cells, or None once the profile kernels' machine code differs from
+    that measured (hash over both kernels, written by the build)."""
     try:
         note = open(TRAFFIC_NOTE).read()
         built = open(KERNEL_HASH).read().strip()
@@ -64,9 +64,24 @@ def measured_traffic(cells_per_launch, field="hbm bytes per cell"):
         if ":" in line and line.startswith("- "):
             key, _, val = line[2:].partition(":")
             fields[key.strip()] = val.strip().strip("`")
-    if fields.get("k_profile code sha256") != built or field not in fields:
+    if fields.get("profile kernels code sha256") != built or field not in fields:
         return None
     return float(fields[field]) * cells_per_launch
+
+
+def profile_kernel(n, m, l, builtin):
+    """The profile kernel that runs a search of length m at the default rank, and
+    what its geometry in use is: strips of the streaming kernel on the built-in
+    geometry (`builtin`, its code), else the tiled kernel's tiles."""
+    from paper_2401_13680_amd import _lib, api, synth
+    import ctypes
+    w = m - l + 1
+    g = api.decode_geometry(api.geometry(w))
+    i32, i64 = ctypes.c_int32, ctypes.c_int64
+    if api.geometry(w) == builtin and _lib.load().pst_host_streams(
+            i32(w), i32(synth.default_k(m)), i64(n - m + 1), i64(n // m)):
+        return dict(kernel="k_stream", windows_per_strip=g["subtile_windows"])
+    return dict(kernel="k_profile", **g)
 
 
 def cpu_baseline(x, m, l, k, nseg_sample=20):
@@ -476,12 +491,13 @@ def serve_bench(args):
     # tile geometry of each m of the stream, tuned on a series of the same
     # generator that is not part of the stream (both paths below use it)
     geometry = {}
+    builtin = {m: api.geometry(m - m // 2 + 1) for m in sorted({r.m for r in reqs})}
     progress(f"{nreq} requests, {cells:.3g} cells; tuning tile geometries")
     if not args.no_tune:
         for m in sorted({r.m for r in reqs}):
             xt = synth.regime_series(200_000, 900 + m, synth.SHAPES5).x
-            code, _ = api.tune_geometry(torch.from_numpy(xt).cuda(), m, m // 2)
-            geometry[str(m)] = api.decode_geometry(code)
+            api.tune_geometry(torch.from_numpy(xt).cuda(), m, m // 2)
+            geometry[str(m)] = profile_kernel(200_000, m, m // 2, builtin[m])
     if args.plain_only:  # the plain pass alone (for profiler runs of its profile launches)
         progress("plain pass")
         ctx = api.context(0)
@@ -579,7 +595,8 @@ def serve_bench(args):
         a[0] += cells_of(r)
         a[1] += t
         a[2] += 1
-    kernel_by_m = {str(m): dict(requests=a[2], cells_per_s=a[0] / (a[1] * 1e-3), geometry=hex(api.geometry(m - m // 2 + 1)))
+    kernel_by_m = {str(m): dict(requests=a[2], cells_per_s=a[0] / (a[1] * 1e-3), geometry=hex(api.geometry(m - m // 2 + 1)),
+                                kernel=profile_kernel(200_000, m, m // 2, builtin[m])["kernel"])
                    for m, a in sorted(per_m.items())}
     out = dict(metric="MPdist distance-matrix cells/sec on 1 MI355X; p50/p99 request latency",
                value=cells / sat, unit="cells/s", n_gpus=1, steps=args.steps, warmup=args.warmup,
