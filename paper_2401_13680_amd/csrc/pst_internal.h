@@ -103,7 +103,7 @@ size_t profile_scratch_bound(int64_t Nm, int64_t nq, int32_t w, bool full = true
 // set).
 constexpr int kStreamKinds = 5;
 constexpr int kStreamNarrow = 178;   // the widest of the narrow kinds, which share a launch: the built-in
-                                     // strips are 992 windows to here, 1984 past it
+                                     // strips are 992 windows to here, 1984 to w = 513, then 992 again
 bool stream_takes(int32_t w, int32_t SBW);
 bool stream_ranks(int32_t w, int32_t k);
 size_t stream_slot_floats(int32_t w, int32_t wmax, int32_t SBW);

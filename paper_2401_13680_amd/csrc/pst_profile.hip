@@ -1376,6 +1376,8 @@ hipError_t launch_profile_batch(const ProfileJob *jobs, int n, int32_t grid, uin
     // windows a workgroup has six waves, and at the narrow kinds' registers a
     // second one does not fit the CU's SIMDs (lengths 64 and 900 in one launch,
     // 100 000 points: 45.7 -> 31.0 ms; 128, 256, 512, 1024, 50 000: 14.8 -> 11.1).
+    // Wider ones take the strips of the widest: w = 179 .. 513 have 992 windows to a
+    // strip beside w > 513, 1984 alone.
     ProfileJob strips[2][kMaxJobs];
     int ns[2] = {0, 0};
     Geo gs[2] = {geo_heuristic(std::min(wmax, kStreamNarrow)), g};

@@ -30,11 +30,14 @@
 //
 // Exact for any input: nothing is guessed that is not a bound.
 //
-// What bounds it: VALU issue.  At w = 129 (100 000 points, m = 256) the launch
-// takes 7.9 ms where k_profile takes 12.6: 44 vector instructions per 64 cells
-// (2 set-up and anchors, 8 first pass, 9 bounds, 5 second pass, 20 selection)
-// and 3.5 B of HBM traffic a cell, where k_profile moves 9.9 B a cell and is
-// held by that.
+// What bounds it: at w <= 178 VALU issue, past it latency (two or four waves a
+// SIMD, few enough that no unit is full).  Vector instructions per 64 cells, their
+// share of the issue rate and bytes of HBM traffic a cell (k_profile: 42, 0.42 and
+// 9.9 at w = 129, and held by the traffic), and ms against k_profile's:
+//   w = 33, 50 000 points of a regime series    104   0.70   8.4    4.9 /  6.4
+//   w = 129, 100 000                             38   0.75   3.1    6.5 / 12.6
+//   w = 257, a walk of 200 000                   35   0.44   7.0   40.6 / 52
+//   w = 513, 100 003                             26   0.34   4.0    9.9 / 18.8
 //
 // A strip's windows reach w-1 columns into the next strip, and the column
 // minima there are the next strip's (k_profile's rule, except at the end of a
@@ -81,7 +84,8 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;  // never counted
 // Columns per group: at most w/2, so that every window holds a whole group, and
 // small against w, so that a block's bounds stay tight, while the group minima
 // of a strip leave LDS for the next workgroup.  For w =
-// 179 .. 264 (strips of 1984 windows, two workgroups a CU) they are kept as
+// 179 .. 264 (strips of 1984 windows, two workgroups a CU; of 992 beside jobs past
+// w = 513) they are kept as
 // their upper 16 bits, rounded down: 24 columns in the space of 48 (w = 257,
 // 100 000 points, l = 256: 11.2 -> 9.3 ms; 200 000 points of a walk: 61 -> 46).
 // Wider strips fill a CU's LDS either way; there whole keys of 48 columns are
@@ -782,9 +786,10 @@ __device__ __forceinline__ void block_bounds(int a0, int a1, int w, int k, int C
 // upper half; those below it count as 0, those above it not at all.  Mostly the
 // value is then known, where all those rows' pieces were kept and selected among
 // (30 000 points, 40 000 at w = 264, l = m/2, before -> now, k_profile; a quarter of
-// a regime series constant: w = 230: 3.0 -> 1.25, 2.4 ms, w = 264: 4.8 -> 2.6, 3.6;
+// a regime series constant: w = 230: 3.0 -> 1.25, 2.4 ms, w = 264: 4.8 -> 1.8, 3.6;
 // period 40, with the blocks at y = 0 that block_bounds settles: w = 230: 4.4 ->
-// 0.54, 1.9, w = 264: 6.9 -> 1.3, 2.6; a walk of 200 000, w = 257: 43.1 -> 41.3).
+// 0.54, 1.9, w = 264: 6.9 -> 0.9, 2.6; a walk of 200 000, w = 257: 43.1 -> 41.3;
+// w = 264 with the second workgroup that its CUs hold now).
 template <int G, int NR>
 __device__ __forceinline__ void equal_blocks(int a0, int a1, int w, int k, int CS, const Dims &d, const uint16_t *bm,
                                              const uint32_t *gm, const uint32_t *colk, uint32_t *need, uint4 *blk,
